@@ -1023,9 +1023,9 @@ mcg_status mcg_plaquette(mcg_ctx *ctx, const mcg_field *U, double *P, void *stre
 template <typename T>
 static mcg_status theta_impl(mcg_ctx *ctx, const mcg_field *W, double *theta, hipStream_t s) {
   const Geom g = geom_of(W->d);
-  const int bs = 256, nb = nblocks(g, bs);
+  const int bs = 256, nb = nblocks(g, bs), npart = nb * (bs / 64);  // one partial sum per wavefront
   mcg_status st;
-  if ((st = ensure(ctx, ctx->part, sizeof(double) * nb)) || (st = ensure(ctx, ctx->states, sizeof(FixState))) ||
+  if ((st = ensure(ctx, ctx->part, sizeof(double) * npart)) || (st = ensure(ctx, ctx->states, sizeof(FixState))) ||
       (st = ensure(ctx, ctx->desc, sizeof(LatDesc<T>))) ||
       (st = ensure_pinned(ctx, sizeof(LatDesc<T>) + sizeof(FixState))))
     return st;
@@ -1037,6 +1037,7 @@ static mcg_status theta_impl(mcg_ctx *ctx, const mcg_field *W, double *theta, hi
   hD->W = (V2<T> *)W->ptr;
   hD->st = (FixState *)ctx->states.p;
   hD->part = (double *)ctx->part.p;
+  hD->npart = npart;
   HIPCHK(hipMemcpyAsync(ctx->desc.p, hD, sizeof(LatDesc<T>), hipMemcpyHostToDevice, s));
   HIPCHK(launch_theta<T>(bs, false, ctx->desc.p, 1, nb, s));
   HIPCHK(launch_book<T>(ctx->desc.p, 1, BOOK_THETA, s));
