@@ -105,6 +105,33 @@ template <typename T> struct LoopImage {
 };
 // images per batched Wilson-loop launch (each holds two line fields)
 constexpr int LOOP_IMAGES_PER_LAUNCH = 16;
+// the images of a launch of the temporal-gauge kernels, passed by value
+struct LoopPath {
+  int n;
+  int d[3];
+  signed char s[MAX_PATH];
+  double weight;
+};
+struct LoopImages {
+  int n;
+  LoopPath img[LOOP_IMAGES_PER_LAUNCH];
+};
+// How the temporal-gauge kernels cover (t, T): blocks of nw waves for nseg ranges of `own` slices
+// each (ok = false: tmax is beyond what a block can hold, or the launch would be too wide)
+struct WlPlan {
+  bool ok;
+  int TE, own, nseg, nw, nblk;
+};
+template <typename T> WlPlan wl_plan(const Geom &g, int tmax);
+// the spatial links in the gauge into N (3 * TE * 9 * Vs complex of T), by way of H (TE * 9 * Vs complex
+// double); *flag is set where a time link is not unitary
+template <typename T>
+hipError_t launch_wl_links(const Geom &g, const void *U, void *H, void *N, int TE, int *flag, hipStream_t s);
+// every image's line, and all (k, T) loop sums of the launch added into res[(k - 1) tmax + T - 1];
+// A holds imgs.n * TE * 9 * Vs complex of T, part imgs.n * rmax * tmax * plan.nblk doubles
+template <typename T>
+hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs, const WlPlan &plan,
+                           int rmax, int tmax, void *A, double *part, double *res, const int *flag, hipStream_t s);
 template <typename T>
 hipError_t launch_vortex_field(const Geom &g, const void *U, const double *G, const int8_t *Z, int mode, void *out,
                                hipStream_t s);

@@ -5,6 +5,8 @@
 //   W(R, T) = < Re tr(loop) / 3 >, the spatial side a path of unit steps
 //   (built as a line field by k_line), the time sides straight.
 
+#include <algorithm>
+
 #include "loops_kernels.hpp"
 
 namespace mcg {
@@ -39,12 +41,67 @@ hipError_t launch_zero(double *p, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <typename T> WlPlan wl_plan(const Geom &g, int tmax) {
+  constexpr int R = WlTile<T>::R, Q = WlTile<T>::Q;
+  WlPlan p{};
+  const int Lt = g.L[3], Vs = g.L[0] * g.L[1] * g.L[2];
+  p.TE = Lt + tmax;
+  // a block holds its own slices and tmax more, and sums the loops of its own
+  const int waves = wl_waves<T>(tmax), most = std::min(waves * R - tmax, waves * Q);
+  if (most < Q) return p;
+  p.nseg = (Lt + most - 1) / most;
+  p.own = (Lt + p.nseg - 1) / p.nseg;
+  p.nseg = (Lt + p.own - 1) / p.own;
+  p.nw = std::max((p.own + tmax + R - 1) / R, (p.own + Q - 1) / Q);
+  p.nblk = p.nseg * ((Vs + 63) / 64);
+  p.ok = true;
+  return p;
+}
+
+template <typename T>
+hipError_t launch_wl_links(const Geom &g, const void *U, void *H, void *N, int TE, int *flag, hipStream_t s) {
+  const int Vs = g.L[0] * g.L[1] * g.L[2];
+  k_wl_gauge<T><<<(Vs + 63) / 64, 64 * WL_WAVES, 0, s>>>(g, (const V2<T> *)U, (double2 *)H, TE, flag);
+  k_wl_links<T><<<TE * ((Vs + 255) / 256), 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)H, TE, (V2<T> *)N, flag);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs, const WlPlan &plan,
+                           int rmax, int tmax, void *A, double *part, double *res, const int *flag, hipStream_t s) {
+  const int Vs = g.L[0] * g.L[1] * g.L[2];
+  const dim3 gl(plan.TE * ((Vs + 255) / 256), imgs.n), gc(plan.nblk, imgs.n);
+  k_wl_line<T><<<gl, 256, 0, s>>>(g, (const V2<T> *)N, imgs, plan.TE, (V2<T> *)A, flag);
+#define MCG_WL(TC, NW) \
+  k_wl_corr<T, TC, NW><<<gc, 64 * plan.nw, 0, s>>>(g, (const V2<T> *)A, imgs, plan.TE, plan.own, rmax, tmax, part, flag)
+  // extents at once: the smallest set that holds tmax, else rounds of 16
+  const bool four = wl_waves<T>(tmax) == 4;
+  if (tmax <= 4) {
+    if (four) MCG_WL(4, 4); else MCG_WL(4, 8);
+  } else if (tmax <= 8) {
+    if (four) MCG_WL(8, 4); else MCG_WL(8, 8);
+  } else if (tmax <= 10) {
+    if (four) MCG_WL(10, 4); else MCG_WL(10, 8);
+  } else if (tmax <= 12) {
+    if (four) MCG_WL(12, 4); else MCG_WL(12, 8);
+  } else {
+    if (four) MCG_WL(16, 4); else MCG_WL(16, 8);
+  }
+#undef MCG_WL
+  k_wl_final<<<rmax * tmax, 256, 0, s>>>(part, plan.nblk, imgs, rmax * tmax, res, flag);
+  return hipGetLastError();
+}
+
 #define MCG_LOOPS_INST(T)                                                                                  \
   template hipError_t launch_vortex_field<T>(const Geom &, const void *, const double *, const int8_t *, int, \
                                              void *, hipStream_t);                                         \
   template hipError_t launch_lines<T>(const Geom &, const void *, const LoopImage<T> *, int, int, hipStream_t); \
   template hipError_t launch_wloops<T>(const Geom &, const void *, const LoopImage<T> *, int, int, int, double *, \
-                                       double *, hipStream_t);
+                                       double *, hipStream_t);                                             \
+  template WlPlan wl_plan<T>(const Geom &, int);                                                           \
+  template hipError_t launch_wl_links<T>(const Geom &, const void *, void *, void *, int, int *, hipStream_t); \
+  template hipError_t launch_wl_loops<T>(const Geom &, const void *, const LoopImages &, const WlPlan &, int, int, \
+                                         void *, double *, double *, const int *, hipStream_t);
 MCG_LOOPS_INST(float)
 MCG_LOOPS_INST(double)
 

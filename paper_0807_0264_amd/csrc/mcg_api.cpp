@@ -147,6 +147,13 @@ mcg_status ensure(mcg_ctx *ctx, DevBuf &b, size_t bytes) {
   return MCG_OK;
 }
 
+// give a scratch buffer back (waits for the device, as hipFree does)
+void release(mcg_ctx *ctx, DevBuf &b) {
+  if (b.p) (void)hipFree(b.p);
+  ctx->scratch_used -= b.cap;
+  b = DevBuf{};
+}
+
 mcg_status ensure_pinned(mcg_ctx *ctx, size_t bytes) {
   if (ctx->h_pinned_cap >= bytes) return MCG_OK;
   if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
@@ -1839,8 +1846,9 @@ std::vector<std::pair<std::vector<int>, int>> path_images(const std::vector<int>
 }
 
 template <typename T>
-mcg_status wilson_impl(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t *vec, int rmax, int tmax,
+mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t *vec, int rmax, int tmax,
                        double *W, hipStream_t s) {
+  // the loops with their time sides multiplied out: any links
   const Geom g = geom_of(U->d);
   const size_t line_bytes = (size_t)g.V * 9 * 2 * sizeof(T);
   const int nres = nvec * rmax * tmax;
@@ -1893,6 +1901,80 @@ mcg_status wilson_impl(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t
   HIPCHK(hipMemcpyAsync(W, res, sizeof(double) * nres, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   return MCG_OK;
+}
+
+// The loops in the temporal gauge (loops_kernels.hpp): *done is false, and nothing is written to W,
+// when the extents or the scratch do not allow it or a time link is not unitary; the general path
+// then takes the call.  At most as many images share a launch as keep the scratch within that of the
+// general path.
+template <typename T>
+mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t *vec, int rmax, int tmax,
+                         double *W, hipStream_t s, bool *done) {
+  *done = false;
+  const Geom g = geom_of(U->d);
+  const WlPlan plan = wl_plan<T>(g, tmax);
+  if (!plan.ok) return MCG_OK;
+  const size_t Vs = (size_t)g.L[0] * g.L[1] * g.L[2];
+  const size_t hbytes = Vs * plan.TE * 9 * sizeof(double2), abytes = Vs * plan.TE * 9 * sizeof(V2<T>);
+  const size_t pbytes = sizeof(double) * (size_t)rmax * tmax * plan.nblk;
+  const int nres = nvec * rmax * tmax;
+  const size_t budget = (size_t)4 << 30;
+  const int ni = (int)std::max<size_t>(
+      1, std::min<size_t>(LOOP_IMAGES_PER_LAUNCH, (budget - std::min(budget, 3 * abytes)) / (abytes + pbytes)));
+  {
+    const std::string err = ctx->err;
+    // the transform h is needed before the first line and shares its space
+    if (ensure(ctx, ctx->line_a, std::max(hbytes, abytes * ni)) || ensure(ctx, ctx->line_b, 3 * abytes) ||
+        ensure(ctx, ctx->wl_part, pbytes * ni) || ensure(ctx, ctx->wl_res, sizeof(double) * (size_t)nres + 64)) {
+      ctx->err = err;  // no room: the general path, with its own scratch
+      for (DevBuf *b : {&ctx->line_a, &ctx->line_b, &ctx->wl_part, &ctx->wl_res}) release(ctx, *b);
+      return MCG_OK;
+    }
+  }
+  mcg_status st;
+  if ((st = ensure_pinned(ctx, 64))) return st;
+  int *flag = (int *)ctx->wl_res.p;             // in front of the results, cleared with them
+  double *res = (double *)ctx->wl_res.p + 8;
+  HIPCHK(launch_zero((double *)ctx->wl_res.p, nres + 8, s));
+  HIPCHK(launch_wl_links<T>(g, U->ptr, ctx->line_a.p, ctx->line_b.p, plan.TE, flag, s));
+  for (int i = 0; i < nvec; i++) {
+    const int v[3] = {vec[3 * i], vec[3 * i + 1], vec[3 * i + 2]};
+    const auto imgs = path_images(staircase_steps(v));
+    int nimg = 0;
+    for (const auto &e : imgs) nimg += e.second;
+    for (size_t c0 = 0; c0 < imgs.size(); c0 += ni) {
+      LoopImages set;
+      memset(&set, 0, sizeof set);
+      set.n = (int)std::min<size_t>(ni, imgs.size() - c0);
+      for (int j = 0; j < set.n; j++) {
+        const auto &e = imgs[c0 + j];
+        LoopPath &d = set.img[j];
+        d.n = (int)e.first.size();
+        for (int q = 0; q < d.n; q++) {
+          d.s[q] = (signed char)e.first[q];
+          d.d[std::abs(e.first[q]) - 1] += e.first[q] > 0 ? 1 : -1;
+        }
+        // Re tr / 3, averaged over sites and images
+        d.weight = (double)e.second / (3.0 * (double)nimg * (double)g.V);
+      }
+      HIPCHK(launch_wl_loops<T>(g, ctx->line_b.p, set, plan, rmax, tmax, ctx->line_a.p,
+                                (double *)ctx->wl_part.p, res + (size_t)i * rmax * tmax, flag, s));
+    }
+  }
+  int *hflag = (int *)ctx->h_pinned;
+  HIPCHK(hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(W, res, sizeof(double) * nres, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  *done = *hflag == 0;
+  return MCG_OK;
+}
+
+template <typename T>
+mcg_status wilson_impl(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t *vec, int rmax, int tmax,
+                       double *W, hipStream_t s) {
+  bool done = false;
+  const mcg_status st = wilson_gauged<T>(ctx, U, nvec, vec, rmax, tmax, W, s, &done);
+  return st || done ? st : wilson_general<T>(ctx, U, nvec, vec, rmax, tmax, W, s);
 }
 
 }  // namespace

@@ -33,6 +33,35 @@ def path_theta():
             assert abs(got - want) <= (1e-12 if prec == 0 else 1e-5) * want, (L, prec, got, want)
 
 
+def loop_field(L, seed, prec, bad=None):
+    """A thermalised field; bad: one time link made non-unitary (a factor) so that the temporal gauge
+    does not apply."""
+    U = rounded(field(L, seed, 2), prec)
+    if bad is not None:
+        U[1, 0, 1, 1, 3] *= bad
+    return U
+
+
+def path_loops():
+    """Wilson loops at the edges of the temporal-gauge kernels: several rounds of 16 extents, time
+    ranges split over blocks, extents beyond a block (the general kernels), spatial sizes below and
+    above a wave, a non-unitary time link (general kernels) and a non-unitary spatial link."""
+    cases = [((2, 2, 2, 20), 1, 20, None), ((6, 4, 4, 6), 2, 3, None), ((2, 2, 2, 34), 1, 30, None),
+             ((2, 2, 2, 60), 1, 60, None), ((4, 2, 2, 8), 1, 8, 1.001)]
+    for L, rmax, tmax, bad in cases:
+        for prec in (0, 1):
+            U = loop_field(L, 2200, prec, bad)
+            if bad is None:
+                U[0, 1, 0, 1, 0] = 0.9 * U[0, 1, 0, 1, 0]
+                U = rounded(U, prec)
+            vecs = [(1, 0, 0), (1, 1, 0)] if L[0] > 2 else [(1, 0, 0)]
+            got = E.wilson_loops(E.links(U, prec), vecs, rmax, tmax)
+            want = O.wilson_loops(U, vecs, rmax, tmax)
+            # FP32: the products of a loop round at 6e-8 each, averaged over few sites
+            err = np.abs(got - want).max()
+            assert err < (1e-13 if prec == 0 else 2e-6), (L, prec, tmax, bad, err)
+
+
 if __name__ == "__main__":
     for name in sys.argv[1:]:
         globals()["path_" + name]()

@@ -8,7 +8,7 @@ import pytest
 
 from test_emu import EMU, emu_lib  # noqa: F401
 
-PATHS = ["theta"]
+PATHS = ["theta", "loops"]
 
 
 @pytest.mark.parametrize("path", PATHS)
