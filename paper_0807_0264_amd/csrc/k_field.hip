@@ -11,20 +11,24 @@ int field_blocks256(const Geom &g) { return (g.Vh + 255) / 256; }
 
 template <typename Tin, typename Tout>
 hipError_t launch_pack_links(const Geom &g, const void *src, void *dst, hipStream_t s) {
-  k_pack_links<Tin, Tout><<<(4 * g.V + 255) / 256, 256, 0, s>>>(g, (const V2<Tin> *)src, (V2<Tout> *)dst);
+  constexpr int H = PackTile<Tout, 4>::H;
+  k_pack<Tin, Tout, 4><<<(g.Vh + H - 1) / H, 256, 0, s>>>(g, (const V2<Tin> *)src, (V2<Tout> *)dst);
   return hipGetLastError();
 }
 template <typename Tin, typename Tout>
 hipError_t launch_unpack_links(const Geom &g, const void *src, void *dst, hipStream_t s) {
-  k_unpack_links<Tin, Tout><<<(4 * g.V + 255) / 256, 256, 0, s>>>(g, (const V2<Tin> *)src, (V2<Tout> *)dst);
+  constexpr int H = PackTile<Tin, 4>::H;
+  k_unpack<Tin, Tout, 4><<<(g.Vh + H - 1) / H, 256, 0, s>>>(g, (const V2<Tin> *)src, (V2<Tout> *)dst);
   return hipGetLastError();
 }
 hipError_t launch_pack_gauge(const Geom &g, const double *src, double *dst, hipStream_t s) {
-  k_pack_gauge<<<(g.V + 255) / 256, 256, 0, s>>>(g, (const double2 *)src, (double2 *)dst, 0);
+  constexpr int H = PackTile<double, 1>::H;
+  k_pack<double, double, 1><<<(g.Vh + H - 1) / H, 256, 0, s>>>(g, (const double2 *)src, (double2 *)dst);
   return hipGetLastError();
 }
 hipError_t launch_unpack_gauge(const Geom &g, const double *src, double *dst, hipStream_t s) {
-  k_pack_gauge<<<(g.V + 255) / 256, 256, 0, s>>>(g, (const double2 *)src, (double2 *)dst, 1);
+  constexpr int H = PackTile<double, 1>::H;
+  k_unpack<double, double, 1><<<(g.Vh + H - 1) / H, 256, 0, s>>>(g, (const double2 *)src, (double2 *)dst);
   return hipGetLastError();
 }
 hipError_t launch_gauge_identity(const Geom &g, double *G, hipStream_t s) {
