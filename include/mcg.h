@@ -396,7 +396,7 @@ mcg_status mcg_center_project(mcg_ctx *ctx, const mcg_field *U, const mcg_gauge 
 /* mcg_center_project for callers that cannot allocate device memory (code under
  * HIP graph capture, serving loops, harnesses that forbid hipMalloc): the same
  * Z and *min_margin, bit for bit, but no call allocates anything.  The
- * per-block minima live in a static 512 KiB scratch array of the library,
+ * per-block minima live in a static 576 KiB scratch array of the library,
  * one per GPU (held until the process ends), so lattices of at most 2^25
  * sites are accepted (larger: MCG_EINVAL; use mcg_center_project).
  * min_margin NULL: nothing is copied back and the stream is not

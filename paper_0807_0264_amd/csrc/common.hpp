@@ -310,21 +310,42 @@ __device__ __forceinline__ int xcd_range(int i, int n) {
   const int x = i & 7, q = n >> 3, r = n & 7;
   return x * q + (x < r ? x : r) + (i >> 3);
 }
-// Tiles of the gather kernels (smearing and its adjoint): a tile is 128 half-sites of one t-slice
-// (S = Vh / Lt half-sites per slice, ceil(S / 128) tiles each).  Tiles come in groups of up to
+// Tiles of the gather kernels (smearing and its adjoint): a tile is TL (128) half-sites of one t-slice
+// (S = Vh / Lt half-sites per slice, ceil(S / TL) tiles each).  Tiles come in groups of up to
 // eight consecutive t-slices, and inside a group the slice index runs fastest, so the tiles that
 // hold a site's t-neighbours are a few tiles away, not a whole slice (at 32^3x64 a slice of links
 // is larger than an XCD's L2).  gather_site maps (tile, lane) to the half-site index, or -1 for the
-// idle lanes of a slice's last tile; a bijection of [0, gather_tiles) x [0, 128) onto the
+// idle lanes of a slice's last tile; a bijection of [0, gather_tiles) x [0, TL) onto the
 // half-sites and the idle lanes.
-__host__ __device__ inline int gather_tiles(const Geom &g) { return g.L[3] * ((g.Vh / g.L[3] + 127) / 128); }
-__device__ __forceinline__ int gather_site(const Geom &g, int tile, int lane) {
-  const int S = g.Vh / g.L[3], span = 8 * ((S + 127) / 128);
+template <int TL = 128> __host__ __device__ inline int gather_tiles(const Geom &g) {
+  return g.L[3] * ((g.Vh / g.L[3] + TL - 1) / TL);
+}
+template <int TL = 128> __device__ __forceinline__ int gather_site(const Geom &g, int tile, int lane) {
+  const int S = g.Vh / g.L[3], span = 8 * ((S + TL - 1) / TL);
   const int gi = tile / span, rem = tile - gi * span;
   const int bt = g.L[3] - 8 * gi < 8 ? g.L[3] - 8 * gi : 8;
   const int ch = rem / bt, t = 8 * gi + (rem - ch * bt);
-  const int s = ch * 128 + lane;
+  const int s = ch * TL + lane;
   return s < S ? t * S + s : -1;
+}
+// The kernels that read G at a site and its forward neighbours (gauge transform, projection, vortex
+// fields; one thread per half index, both parities) take the same tiles with 256 lanes, each XCD a
+// contiguous range of them, and let the links, touched once, pass by with streaming accesses: more
+// of the neighbours' G then comes from L2.  (Both parities of a tile in the two halves of a block
+// read fewer bytes, 1.35 instead of 1.52 GB for a 32^3x64 projection of 0.91, but took 263 us instead
+// of 228.)
+// Slices of fewer than 2048 half-sites (295 KB of G per parity) fit an L2 several times over as they
+// are, and would leave too many lanes of their last tile idle; they stay lexicographic.
+__host__ __device__ inline bool site_tiled(const Geom &g) { return g.Vh / g.L[3] >= 2048; }
+__host__ __device__ inline int site_blocks(const Geom &g) {
+  return site_tiled(g) ? gather_tiles<256>(g) : (g.Vh + 255) / 256;
+}
+// the half-site of this thread in a launch of site_blocks(g) blocks of 256, or -1
+__device__ __forceinline__ int site_of_block(const Geom &g) {
+  const int tile = xcd_range((int)blockIdx.x, (int)gridDim.x);
+  if (site_tiled(g)) return gather_site<256>(g, tile, (int)threadIdx.x);
+  const int h = tile * 256 + (int)threadIdx.x;
+  return h < g.Vh ? h : -1;
 }
 __device__ __forceinline__ int lex_index(const Geom &g, const int c[4]) {
   return c[0] + g.L[0] * (c[1] + g.L[1] * (c[2] + g.L[2] * c[3]));
@@ -421,6 +442,27 @@ template <typename T> struct Links {
   __device__ __forceinline__ M3<T> load(int mu, int par, int h) const { return load_off(mu, off(par, h)); }
   __device__ __forceinline__ void store(int mu, int par, int h, const M3<T> &m) const {
     store_off(mu, off(par, h), m);
+  }
+  // streaming forms, for links touched once next to data that should stay in the caches
+  __device__ __forceinline__ M3<T> load_stream(int mu, int par, int h) const {
+    const unsigned o = off(par, h);
+    M3<T> m;
+#pragma unroll
+    for (int k = 0; k < 9; k++) {
+      const V2<T> v = ld_plane_stream(p + (size_t)(mu * 18 + k) * Vh, o);
+      m.e[k] = cx<T>{v.x, v.y};
+    }
+    return m;
+  }
+  __device__ __forceinline__ void store_stream(int mu, int par, int h, const M3<T> &m) const {
+    const unsigned o = off(par, h);
+#pragma unroll
+    for (int k = 0; k < 9; k++) {
+      V2<T> v;
+      v.x = m.e[k].re;
+      v.y = m.e[k].im;
+      st_plane_stream(p + (size_t)(mu * 18 + k) * Vh, o, v);
+    }
   }
   // link mu at the site with coordinates c
   __device__ __forceinline__ M3<T> at(const Geom &g, const int c[4], int mu) const {

@@ -76,7 +76,7 @@ template <typename T>
 hipError_t launch_smear_step(const Geom &g, const void *U, void *out, double rho, double eps,
                              hipStream_t s, void *Cst = nullptr);
 
-// k_project.hip -- centre projection and vortex counting
+// k_project.hip -- centre projection (part: site_blocks(g) doubles) and vortex counting
 template <typename T>
 hipError_t launch_center_project(const Geom &g, const void *U, const double *G, int8_t *Z,
                                  double *part, double *min_out, hipStream_t s);

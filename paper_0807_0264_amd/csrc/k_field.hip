@@ -41,7 +41,7 @@ hipError_t launch_gauge_reunit(const Geom &g, double *G, hipStream_t s) {
 }
 template <typename T>
 hipError_t launch_apply_gauge(const Geom &g, const void *U, const double *G, void *out, hipStream_t s) {
-  k_apply_gauge<T><<<field_blocks256(g), 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, (V2<T> *)out);
+  k_apply_gauge<T><<<site_blocks(g), 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, (V2<T> *)out);
   return hipGetLastError();
 }
 template <typename T>

@@ -14,7 +14,7 @@ namespace mcg {
 template <typename T>
 hipError_t launch_vortex_field(const Geom &g, const void *U, const double *G, const int8_t *Z, int mode, void *out,
                                hipStream_t s) {
-  k_vortex_field<T><<<(g.Vh + 255) / 256, 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, Z, mode,
+  k_vortex_field<T><<<site_blocks(g), 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, Z, mode,
                                                       (V2<T> *)out);
   return hipGetLastError();
 }

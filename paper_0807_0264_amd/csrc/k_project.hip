@@ -15,14 +15,18 @@ namespace mcg {
 template <typename T>
 hipError_t launch_center_project(const Geom &g, const void *U, const double *G, int8_t *Z,
                                  double *part, double *min_out, hipStream_t s) {
-  const int nb = field_blocks256(g);
-  k_center_project<T><<<nb, 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, Z, part);
-  k_min_final<<<1, 256, 0, s>>>(part, nb, min_out);
+  const int nb = site_blocks(g), pairs = ((uintptr_t)Z & 1) == 0;
+  k_center_project<T><<<nb, 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, Z, part, pairs);
+  k_min_final<<<1, 1024, 0, s>>>(part, nb, min_out);
   return hipGetLastError();
 }
 
 hipError_t launch_count_vortices(const Geom &g, const int8_t *Z, unsigned long long *counts,
                                  hipStream_t s) {
+  if (g.L[0] % 4 == 0 && ((uintptr_t)Z & 3) == 0) {  // four sites per thread, in words
+    k_count_vortices4<<<std::min((g.V / 4 + 255) / 256, 1024), 256, 0, s>>>(g, Z, counts);
+    return hipGetLastError();
+  }
   // a few blocks per CU, each site visited by one thread of a grid-stride loop
   const int blocks = std::min((g.V + 255) / 256, 2048);
   k_count_vortices<<<blocks, 256, 0, s>>>(g, Z, counts);

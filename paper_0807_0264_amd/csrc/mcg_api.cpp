@@ -62,10 +62,13 @@ struct mcg_ctx {
 };
 
 // Scratch of the allocation-free centre projection (mcg_center_project_noalloc): the per-block
-// minima of the centre-phase margin, one per 256 half sites, then the final minimum.  Every GPU the
-// library runs on holds its own copy until the process ends.  In host code `scratch` names a
+// minima of the centre-phase margin, one per tile of 256 half sites, then the final minimum.  Every GPU
+// the library runs on holds its own copy until the process ends.  In host code `scratch` names a
 // host-side stand-in: the kernels get this device's address of it, looked up once per device.
-constexpr int NOALLOC_PARTS = 65536;  // ceil(V / 512) <= 65536: lattices of up to 2^25 sites
+constexpr int NOALLOC_SITES = 1 << 25;  // lattices of up to 2^25 sites ...
+// ... have at most 2^16 tiles, and a ragged last tile per slice (of 2048 half sites or more) adds less
+// than an eighth
+constexpr int NOALLOC_PARTS = NOALLOC_SITES / 512 / 8 * 9;
 static __device__ __align__(256) double scratch[NOALLOC_PARTS + 32];
 
 namespace {
@@ -669,7 +672,7 @@ static mcg_status precondition_impl(mcg_ctx *ctx, int B, const mcg_field *U, dou
   // every field's projection and count, then one copy back
   const Range range_("project and count");
   std::vector<size_t> p0(B + 1, 0);
-  for (int b = 0; b < B; b++) p0[b + 1] = p0[b] + (size_t)field_blocks256(geom_of(U[b].d));
+  for (int b = 0; b < B; b++) p0[b + 1] = p0[b] + (size_t)site_blocks(geom_of(U[b].d));
   if ((st = ensure(ctx, ctx->pc_part, sizeof(double) * (p0[B] + B))) ||
       (st = ensure(ctx, ctx->pc_counts, sizeof(unsigned long long) * 12 * B)) ||
       (st = ensure_pinned(ctx, sizeof(double) * B + sizeof(unsigned long long) * 12 * B)))
@@ -1686,7 +1689,7 @@ mcg_status mcg_center_project(mcg_ctx *ctx, const mcg_field *U, const mcg_gauge 
   if (!Z) return fail(ctx, MCG_EINVAL, "Z is NULL");
   if ((st = check_inputs(ctx, U, G, (hipStream_t)stream))) return st;
   const Geom g = geom_of(U->d);
-  if ((st = ensure(ctx, ctx->part, sizeof(double) * field_blocks256(g))) ||
+  if ((st = ensure(ctx, ctx->part, sizeof(double) * site_blocks(g))) ||
       (st = ensure(ctx, ctx->scalars, 64)))
     return st;
   hipStream_t s = (hipStream_t)stream;
@@ -1712,11 +1715,10 @@ mcg_status mcg_center_project_noalloc(mcg_ctx *ctx, const mcg_field *U, const mc
   if (G && (st = check_gauge(ctx, G, U->d, "G"))) return st;
   if (!Z) return fail(ctx, MCG_EINVAL, "Z is NULL");
   const Geom g = geom_of(U->d);
-  const int nb = field_blocks256(g);
-  if (nb > NOALLOC_PARTS)
+  if (g.V > NOALLOC_SITES)
     return fail(ctx, MCG_EINVAL,
                 "mcg_center_project_noalloc: %d sites exceed its limit of %d (2^25); use mcg_center_project",
-                g.V, 512 * NOALLOC_PARTS);
+                g.V, NOALLOC_SITES);
   if (!ctx->noalloc)
     return fail(ctx, MCG_EHIP, "mcg_center_project_noalloc: no device address of its scratch: %s",
                 ctx->noalloc_err.c_str());
