@@ -149,9 +149,7 @@ __global__ __launch_bounds__(128) void k_step_adj_a(Geom g, const V2<T> *__restr
       Cp = Links<T>{const_cast<V2<T> *>(Cst), g.Vh}.load(mu, par, h);
       Cr = OI ? Links<T>{const_cast<V2<T> *>(Cst) + (size_t)72 * g.Vh, g.Vh}.load(mu, par, h) : m_zero<T>();
     } else {
-      int c[4];
-      coords_of(g, par, h, c);
-      staples<T, OI>(g, L, c, mu, Cp, Cr);
+      staples<T, OI>(g, L, par, h, mu, Cp, Cr);
     }
     // only C and dC/deps stay live through the adjoint of the exponential (C = rho Cu)
     M3<T> C, dC;
@@ -218,7 +216,9 @@ __global__ __launch_bounds__(128) void k_step_adj_a(Geom g, const V2<T> *__restr
 }
 
 // With eps = 1 the rectangle weight vanishes, but dC/deps = rho(-2/3 Cp + 1/12 Cr)
-// still has a rectangle part: <grad_C, rho/12 Cr> per link.
+// still has a rectangle part: <grad_C, rho/12 Cr> per link.  12x12x10x6, FP64: 42 us (64.6 us with sites
+// addressed through their coordinates); a launch of so few waves is bound by fetching its instructions
+// once, and a thread per link and direction nu takes as long.
 template <typename T>
 __global__ __launch_bounds__(128) void k_eps_rect(Geom g, const V2<T> *__restrict__ U,
                                                   const V2<T> *__restrict__ gC, T rho, double *part) {
@@ -229,10 +229,8 @@ __global__ __launch_bounds__(128) void k_eps_rect(Geom g, const V2<T> *__restric
   double deps = 0.0;
   if (h >= 0) {
     const Links<T> L{const_cast<V2<T> *>(U), g.Vh};
-    int c[4];
-    coords_of(g, par, h, c);
     M3<T> Cp, Cr;
-    staples<T, true>(g, L, c, mu, Cp, Cr);
+    staples<T, true>(g, L, par, h, mu, Cp, Cr);
     const M3<T> gc = Links<T>{const_cast<V2<T> *>(gC), g.Vh}.load(mu, par, h);
     deps = (double)rdot(gc, scale(rho * T(1.0 / 12.0), Cr));
   }
@@ -290,38 +288,48 @@ template <bool DAG, typename T> __device__ __forceinline__ void mac_o(const M3<T
   else mac(a, b, c);
 }
 
-// Steps K .. KEND-1 (K >= 1) of loop S (sign SG), from pos (left at the position after them): load
-// f_K and Gam_K, advance the recurrence.  The sign is a template argument, so every dagger is known
-// when the kernel is compiled.
-template <typename T, int S, int SG, int K, int KEND, class LD>
-__device__ __forceinline__ void loop_steps(const Geom &g, const LD &L, const Links<T> &GC, int pos[4], int lam,
-                                           int nu, M3<T> &A, M3<T> &P) {
+// The offsets of the (lam, nu) plane around y: y + a lam + b nu for the a and b that loops meet.
+template <typename T> struct LoopPlane {
+  Around<T> y;
+  int l_1, l1, l2, n_2, n_1, n1, n2;
+  template <int A, int B> __device__ __forceinline__ unsigned off() const {
+    static_assert(A >= -1 && A <= 2 && B >= -2 && B <= 2, "a loop's reach");
+    const int d = (A == -1 ? l_1 : A == 1 ? l1 : A == 2 ? l2 : 0) +
+                  (B == -2 ? n_2 : B == -1 ? n_1 : B == 1 ? n1 : B == 2 ? n2 : 0);
+    return (A + B) & 1 ? y.odd(d) : y.even(d);
+  }
+};
+
+// Steps K .. KEND-1 (K >= 1) of loop S (sign SG), from y + A lam + B nu: load f_K and Gam_K, advance the
+// recurrence.  The sign and the position are template arguments, so every dagger and every site is
+// known when the kernel is compiled.
+template <typename T, int S, int SG, int K, int KEND, int A, int B>
+__device__ __forceinline__ void loop_steps(const Links<T> &L, const Links<T> &GC, const LoopPlane<T> &pl, int lam,
+                                           int nu, M3<T> &D, M3<T> &P) {
   if constexpr (K < KEND) {
     constexpr int sym = Loop<S>::sym[K], sgn = Loop<S>::sgn[K];
-    constexpr bool back = (sym ? sgn * SG : sgn) < 0;
+    constexpr int st = sym ? sgn * SG : sgn;
+    constexpr bool back = st < 0;
+    constexpr int A2 = sym ? A : A + st, B2 = sym ? B + st : B;  // the position after the step
     const int d = sym ? nu : lam;
-    int t[4];
-    moved(g, pos, d, back ? -1 : +1, t);
-    const int *at = back ? t : pos;
-    const M3<T> f = L.at(g, at, d);
-    const M3<T> G = GC.at(g, at, d);
+    const unsigned o = pl.template off<(back ? A2 : A), (back ? B2 : B)>();
+    const M3<T> f = L.load_off(d, o);
+    const M3<T> G = GC.load_off(d, o);
     if constexpr (K == 1) {
       if constexpr (back) {
-        A = dag(G);
+        D = dag(G);
         P = dag(f);
       } else {
-        A = G;
+        D = G;
         P = f;
       }
     } else {
-      M3<T> a = mul_o<back>(A, f);
+      M3<T> a = mul_o<back>(D, f);
       mac_o<back>(P, G, a);
-      A = a;
+      D = a;
       if constexpr (K + 1 < Loop<S>::n) P = mul_o<back>(P, f);
     }
-#pragma unroll
-    for (int q = 0; q < 4; q++) pos[q] = t[q];
-    loop_steps<T, S, SG, K + 1, KEND, LD>(g, L, GC, pos, lam, nu, A, P);
+    loop_steps<T, S, SG, K + 1, KEND, A2, B2>(L, GC, pl, lam, nu, D, P);
   }
 }
 
@@ -332,48 +340,38 @@ template <typename T> __device__ __forceinline__ void add_dag(T w, const M3<T> &
     for (int j = 0; j < 3; j++) acc.e[3 * i + j] = acc.e[3 * i + j] + w * conj(A.e[3 * j + i]);
 }
 
-// opaque copy of start coordinates: keeps the compiler from computing the addresses of every loop
-// at once (a register-pressure hint with no run-time cost)
-__device__ __forceinline__ void opaque_start(const int in[4], int out[4]) {
-#pragma unroll
-  for (int q = 0; q < 4; q++) out[q] = in[q];
-  opaque_coords(out);
+// the plane with opaque offsets: keeps the compiler from computing the addresses of every loop at once
+// (a register-pressure hint with no run-time cost)
+template <typename T> __device__ __forceinline__ LoopPlane<T> opaque_plane(LoopPlane<T> p) {
+  p.y = opaque_site(p.y);
+  return p;
 }
 
 // The loops of one direction nu and sign SG through U_lam(y), added to acc with their weights.
 // S0, S2 and S3 leave m along N through the same link, and S0 and S2 go on along -L through the
 // same link too: those steps are taken once and the loops continue from copies of (A, P).
-template <typename T, bool OI, int SG, class LD>
-__device__ __forceinline__ void loops_of(const Geom &g, const LD &L, const Links<T> &GC, const int yl[4], int lam,
-                                         int nu, T wp, T wr, M3<T> &acc) {
+template <typename T, bool OI, int SG>
+__device__ __forceinline__ void loops_of(const Links<T> &L, const Links<T> &GC, const LoopPlane<T> &p0, int lam, int nu,
+                                         T wp, T wr, M3<T> &acc) {
   M3<T> A, P;
-  {  // S1: L L N -L -L -N
-    if constexpr (OI) {
-      int pos[4];
-      opaque_start(yl, pos);
-      loop_steps<T, 1, SG, 1, 6, LD>(g, L, GC, pos, lam, nu, A, P);
-      add_dag(wr, A, acc);
-    }
+  if constexpr (OI) {  // S1: L L N -L -L -N
+    loop_steps<T, 1, SG, 1, 6, 1, 0>(L, GC, opaque_plane(p0), lam, nu, A, P);
+    add_dag(wr, A, acc);
   }
-  int pos[4];
-  opaque_start(yl, pos);
-  loop_steps<T, 0, SG, 1, 2, LD>(g, L, GC, pos, lam, nu, A, P);  // N, shared by S0, S2, S3
+  LoopPlane<T> pl = opaque_plane(p0);
+  loop_steps<T, 0, SG, 1, 2, 1, 0>(L, GC, pl, lam, nu, A, P);  // N, shared by S0, S2, S3
   if constexpr (OI) {  // S3: L N N -L -N -N
-    int p3[4];
-    opaque_start(pos, p3);
     M3<T> A3 = A, P3 = P;
-    loop_steps<T, 3, SG, 2, 6, LD>(g, L, GC, p3, lam, nu, A3, P3);
+    loop_steps<T, 3, SG, 2, 6, 1, SG>(L, GC, opaque_plane(pl), lam, nu, A3, P3);
     add_dag(wr, A3, acc);
   }
-  loop_steps<T, 0, SG, 2, 3, LD>(g, L, GC, pos, lam, nu, A, P);  // -L, shared by S0 and S2
+  loop_steps<T, 0, SG, 2, 3, 1, SG>(L, GC, pl, lam, nu, A, P);  // -L, shared by S0 and S2
   if constexpr (OI) {  // S2: L N -L -L -N L
-    int p2[4];
-    opaque_start(pos, p2);
     M3<T> A2 = A, P2 = P;
-    loop_steps<T, 2, SG, 3, 6, LD>(g, L, GC, p2, lam, nu, A2, P2);
+    loop_steps<T, 2, SG, 3, 6, 0, SG>(L, GC, opaque_plane(pl), lam, nu, A2, P2);
     add_dag(wr, A2, acc);
   }
-  loop_steps<T, 0, SG, 3, 4, LD>(g, L, GC, pos, lam, nu, A, P);  // S0: L N -L -N
+  loop_steps<T, 0, SG, 3, 4, 0, SG>(L, GC, pl, lam, nu, A, P);  // S0: L N -L -N
   add_dag(wp, A, acc);
 }
 
@@ -390,12 +388,16 @@ __global__ __launch_bounds__(128) void k_step_adj_b(Geom g, const V2<T> *__restr
   coords_of(g, par, h, y);
   M3<T> acc = GU.load(lam, par, h);
   const T wtp = rho * wp, wtr = rho * wr;
-  int yl[4];  // the end of m: every loop's walk starts there
-  moved(g, y, lam, +1, yl);
+  LoopPlane<T> pl{Around<T>(L, par, h), move_by<T>(g, y, lam, -1), move_by<T>(g, y, lam, +1),
+                  OI ? move_by<T>(g, y, lam, +2) : 0};
   for (int nu = 0; nu < 4; nu++) {
     if (nu == lam) continue;
-    loops_of<T, OI, +1, Links<T>>(g, L, GC, yl, lam, nu, wtp, wtr, acc);
-    loops_of<T, OI, -1, Links<T>>(g, L, GC, yl, lam, nu, wtp, wtr, acc);
+    pl.n_1 = move_by<T>(g, y, nu, -1);
+    pl.n1 = move_by<T>(g, y, nu, +1);
+    pl.n_2 = OI ? move_by<T>(g, y, nu, -2) : 0;
+    pl.n2 = OI ? move_by<T>(g, y, nu, +2) : 0;
+    loops_of<T, OI, +1>(L, GC, pl, lam, nu, wtp, wtr, acc);
+    loops_of<T, OI, -1>(L, GC, pl, lam, nu, wtp, wtr, acc);
   }
   GU.store(lam, par, h, acc);
 }

@@ -310,6 +310,15 @@ __device__ __forceinline__ int xcd_range(int i, int n) {
   const int x = i & 7, q = n >> 3, r = n & 7;
   return x * q + (x < r ? x : r) + (i >> 3);
 }
+// a value that is the same in all lanes of a wave, held in a scalar register
+__device__ __forceinline__ int wave_uniform(int x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_readfirstlane(x);
+#else
+  return x;
+#endif
+}
+
 // Tiles of the gather kernels (smearing and its adjoint): a tile is TL (128) half-sites of one t-slice
 // (S = Vh / Lt half-sites per slice, ceil(S / TL) tiles each).  Tiles come in groups of up to
 // eight consecutive t-slices, and inside a group the slice index runs fastest, so the tiles that

@@ -204,15 +204,6 @@ template <> struct WlTile<double> { static constexpr int R = 4, Q = 3; };
 constexpr int WL_WAVES = 8;
 template <typename T> constexpr int wl_waves(int tmax) { return 2 * tmax <= 4 * WlTile<T>::R ? 4 : WL_WAVES; }
 
-// a value that is the same in all lanes of a wave, held in a scalar register
-__device__ __forceinline__ int wave_uniform(int x) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_readfirstlane(x);
-#else
-  return x;
-#endif
-}
-
 // one matrix of a [t][element][s] field, o = s * sizeof(complex)
 template <typename V> struct wl_real;
 template <> struct wl_real<float2> { using type = float; };

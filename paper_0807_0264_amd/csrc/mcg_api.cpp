@@ -765,9 +765,11 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
   {
     const Range range_("backward: forward smearing");
     for (int k = 0; k < n; k++) {
-      if (k % c == 0) HIPCHK(hipMemcpyAsync(slot(k / c), cur, fb, hipMemcpyDeviceToDevice, s));
       const bool in_last = k >= k0_last && k < n - 1;
-      void *nxt = in_last ? slot((size_t)nck + (k - k0_last)) : (cur == tmp0 ? tmp1 : tmp0);
+      // a step whose result is a checkpoint writes it there; U itself is the first one
+      void *nxt = (k + 1) % c == 0 && k + 1 < n ? slot((k + 1) / c)
+                  : in_last                     ? slot((size_t)nck + (k - k0_last))
+                                                : (cur == tmp0 ? tmp1 : tmp0);
       const bool last = k % c == c - 1 || k == n - 1;
       void *cs = last ? clast(k / c) : in_last ? csum(k - k0_last) : nullptr;
       HIPCHK(launch_smear_step<T>(g, cur, nxt, rho, eps, s, cs));
@@ -783,7 +785,7 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
     // step forms (the last step's were kept by the forward pass), which the first pass of the
     // adjoint reads
     std::vector<const void *> fields(len);
-    fields[0] = slot(seg);
+    fields[0] = seg == 0 ? U->ptr : slot(seg);
     for (int j = 1; j < len; j++) {
       void *dst = slot(nck + j - 1);
       if (seg < nck - 1) HIPCHK(launch_smear_step<T>(g, fields[j - 1], dst, rho, eps, s, csum(j - 1)));
@@ -792,12 +794,13 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
     for (int j = len - 1; j >= 0; j--) {
       const int k = k0 + j;
       double *p = part + nb_seed + (size_t)k * 3 * nb_step;
+      if (k == 0) gout = gradU->ptr;  // the last adjoint writes the caller's field
       HIPCHK(launch_step_adjoint<T>(g, fields[j], j == len - 1 ? clast(seg) : csum(j), gin, gout, gC, rho, eps,
                                     p, flag, s));
       std::swap(gin, gout);
     }
   }
-  HIPCHK(hipMemcpyAsync(gradU->ptr, gin, fb, hipMemcpyDeviceToDevice, s));
+  if (n == 0) HIPCHK(hipMemcpyAsync(gradU->ptr, gin, fb, hipMemcpyDeviceToDevice, s));
   HIPCHK(launch_reduce_parts(part, nb_seed, n, nb_step, red, s));
   double h[4];
   HIPCHK(hipMemcpyAsync(h, red, 3 * sizeof(double) + sizeof(int), hipMemcpyDeviceToHost, s));

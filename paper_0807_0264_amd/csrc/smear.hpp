@@ -116,14 +116,58 @@ template <typename T> __device__ __forceinline__ M3<T> exp_su3(const M3<T> &A) {
   return E;
 }
 
-// Make the compiler treat coordinates as freshly produced (see staples).
-__device__ __forceinline__ void opaque_coords(int c[4]) {
+// Byte offsets of the sites x + a mu + b nu (|a|, |b| <= 2) around a site x of parity par, half index h
+// and coordinates c, into the planes of a link field.  Lx is even, so a step along y, z or t moves the
+// half index by a stride whatever x is, a step along x by what (x >> 1) moves, and steps along
+// different directions add: two selections per (direction, steps) and one addition per site, where
+// going from coordinates to an index took three 32-bit multiplications (a quarter of the FMA rate) per
+// site, a tenth of the instructions: per wave, over-improved 9,703 -> 8,845, stout 2,581 -> 2,367.  Stout
+// 32^3x64 FP32 0.823 -> 0.802 ms a step; the over-improved step and the loop gather, which run at the
+// clock that their FMAs allow, 0 and 2.5 % faster.
+template <typename T> struct Around {
+  unsigned same, other;  // x as a site of its own parity; the same half index of the other parity
+  __device__ __forceinline__ Around(const Links<T> &L, int par, int h) : same(L.off(par, h)), other(L.off(1 - par, h)) {}
+  // the offset after an odd (or even) number of steps that moved by d
+  __device__ __forceinline__ unsigned odd(int d) const { return other + (unsigned)d; }
+  __device__ __forceinline__ unsigned even(int d) const { return same + (unsigned)d; }
+};
+// what `step` (|step| <= 2, at most the extent) along direction d moves, in bytes
+template <typename T> __device__ __forceinline__ int move_by(const Geom &g, const int c[4], int d, int step) {
+  const int x = d == 0 ? c[0] : d == 1 ? c[1] : d == 2 ? c[2] : c[3], n = g.L[d];
+  if (d == 0) {
+    int v = x + step;
+    v = v >= n ? v - n : v;
+    v = v < 0 ? v + n : v;
+    return ((v >> 1) - (x >> 1)) * (int)sizeof(V2<T>);
+  }
+  int st = g.hx * (int)sizeof(V2<T>);
+  if (d > 1) st *= g.L[1];
+  if (d > 2) st *= g.L[2];
+  const bool wrap = step > 0 ? x + step >= n : x + step < 0;
+  return wrap ? (step > 0 ? step - n : step + n) * st : step * st;
+}
+// Make the compiler treat a site's offsets as freshly produced (see staples).
+template <typename T> __device__ __forceinline__ Around<T> opaque_site(Around<T> x) {
 #if defined(__HIP_DEVICE_COMPILE__)
-#pragma unroll
-  for (int q = 0; q < 4; q++) __asm__ volatile("" : "+v"(c[q]));
-#else
-  (void)c;
+  __asm__ volatile("" : "+v"(x.same), "+v"(x.other));
 #endif
+  return x;
+}
+
+// ... and, with m, as known only once all of m is: loads from x are not issued before m is computed.
+template <typename T> __device__ __forceinline__ Around<T> opaque_site(Around<T> x, M3<T> &m) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __asm__ volatile(""
+                   : "+v"(x.same), "+v"(x.other), "+v"(m.e[0].re), "+v"(m.e[0].im), "+v"(m.e[1].re),
+                     "+v"(m.e[1].im), "+v"(m.e[2].re), "+v"(m.e[2].im), "+v"(m.e[3].re), "+v"(m.e[3].im));
+  __asm__ volatile(""
+                   : "+v"(x.same), "+v"(x.other), "+v"(m.e[4].re), "+v"(m.e[4].im), "+v"(m.e[5].re),
+                     "+v"(m.e[5].im), "+v"(m.e[6].re), "+v"(m.e[6].im), "+v"(m.e[7].re), "+v"(m.e[7].im),
+                     "+v"(m.e[8].re), "+v"(m.e[8].im));
+#else
+  (void)m;
+#endif
+  return x;
 }
 
 // Make the compiler treat a loaded matrix as produced here: every load into it is complete at this
@@ -145,30 +189,27 @@ template <typename T> __device__ __forceinline__ void opaque_m3(M3<T> &m) {
 // link into x+mu along nu, and every 2x1-ahead path ends on U_mu(x+mu)^dag, so
 // their prefixes are summed first and multiplied by that link once.
 template <typename T, bool OI>
-__device__ __forceinline__ void staples(const Geom &g, const Links<T> &L, const int c[4], int mu,
-                                        M3<T> &Cp, M3<T> &Cr) {
+__device__ __forceinline__ void staples(const Geom &g, const Links<T> &L, int par, int h, int mu, M3<T> &Cp,
+                                        M3<T> &Cr) {
   Cp = m_zero<T>();
   Cr = m_zero<T>();
   M3<T> ahead = m_zero<T>();  // OI: sum of the 2x1-ahead prefixes, closed by U_mu(x+mu)^dag at the end
-  int cpm[4], cmm[4];
-  moved(g, c, mu, +1, cpm);
-  moved(g, c, mu, -1, cmm);
-  const M3<T> umu_xmm = OI ? L.at(g, cmm, mu) : m_zero<T>();  // U_mu(x-mu)
+  int c[4];
+  coords_of(g, par, h, c);
+  const Around<T> x0(L, par, h);
+  const int m1 = move_by<T>(g, c, mu, +1);
   if constexpr (!OI) {
     // Stout: the six links of a direction are loaded together and (FP32) held until all six are in,
     // so a wave has six loads in flight instead of three; 142 VGPRs and three waves per SIMD
     // instead of 94 and five, 1.7 % less time.  The sums are taken in the same order.
     for (int nu = 0; nu < 4; nu++) {
       if (nu == mu) continue;
-      int b[4] = {c[0], c[1], c[2], c[3]}, bpm[4] = {cpm[0], cpm[1], cpm[2], cpm[3]};
-      opaque_coords(b);
-      opaque_coords(bpm);
-      int cpn[4], cmn[4], cmnpm[4];
-      moved(g, b, nu, +1, cpn);
-      moved(g, b, nu, -1, cmn);
-      moved(g, cmn, mu, +1, cmnpm);
-      M3<T> unu_x = L.at(g, b, nu), umu_xpn = L.at(g, cpn, mu), unu_xpm = L.at(g, bpm, nu);  // +nu side
-      M3<T> unu_xmn = L.at(g, cmn, nu), umu_xmn = L.at(g, cmn, mu), unu_xmnpm = L.at(g, cmnpm, nu);  // -nu
+      const Around<T> x = opaque_site(x0);
+      const int n1 = move_by<T>(g, c, nu, +1), n_1 = move_by<T>(g, c, nu, -1);
+      M3<T> unu_x = L.load_off(nu, x.even(0)), umu_xpn = L.load_off(mu, x.odd(n1)),
+            unu_xpm = L.load_off(nu, x.odd(m1));  // +nu side
+      M3<T> unu_xmn = L.load_off(nu, x.odd(n_1)), umu_xmn = L.load_off(mu, x.odd(n_1)),
+            unu_xmnpm = L.load_off(nu, x.even(n_1 + m1));  // -nu
       if constexpr (sizeof(T) == 4) {
         opaque_m3(unu_x);
         opaque_m3(umu_xpn);
@@ -182,80 +223,65 @@ __device__ __forceinline__ void staples(const Geom &g, const Links<T> &L, const 
     }
     return;
   }
+  const int m_1 = move_by<T>(g, c, mu, -1), m2 = move_by<T>(g, c, mu, +2);
+  const M3<T> umu_xmm = L.load_off(mu, x0.odd(m_1));  // U_mu(x-mu)
   for (int nu = 0; nu < 4; nu++) {
     if (nu == mu) continue;
-    // Each side of the direction starts from opaque copies of the base coordinates, so the
+    // Each side of the direction starts from opaque copies of the site's offsets, so the
     // compiler forms its addresses and loads where they are used rather than all at once (a
     // register-pressure hint with no run-time cost); the sums are taken in the same order.
     {  // +nu
-      int b[4] = {c[0], c[1], c[2], c[3]}, bpm[4] = {cpm[0], cpm[1], cpm[2], cpm[3]},
-          bmm[4] = {cmm[0], cmm[1], cmm[2], cmm[3]};
-      opaque_coords(b);
-      opaque_coords(bpm);
-      opaque_coords(bmm);
-      int cpn[4];
-      moved(g, b, nu, +1, cpn);
-      const M3<T> unu_x = L.at(g, b, nu);       // U_nu(x)
-      const M3<T> umu_xpn = L.at(g, cpn, mu);   // U_mu(x+nu)
-      const M3<T> unu_xpm = L.at(g, bpm, nu);   // U_nu(x+mu)
-      const M3<T> up = mul(unu_x, umu_xpn);     // U_nu(x) U_mu(x+nu)
+      Around<T> x = opaque_site(x0, Cr);
+      const int n1 = move_by<T>(g, c, nu, +1), n2 = move_by<T>(g, c, nu, +2);
+      const M3<T> unu_x = L.load_off(nu, x.even(0));     // U_nu(x)
+      const M3<T> umu_xpn = L.load_off(mu, x.odd(n1));   // U_mu(x+nu)
+      const M3<T> unu_xpm = L.load_off(nu, x.odd(m1));   // U_nu(x+mu)
+      M3<T> up = mul(unu_x, umu_xpn);                    // U_nu(x) U_mu(x+nu)
+      x = opaque_site(x, up);
       mac_nd(up, unu_xpm, Cp);
-      if (OI) {
-        int cpnpm[4], cp2m[4], cmmpn[4], cp2n[4];
-        moved(g, cpn, mu, +1, cpnpm);
-        moved(g, bpm, mu, +1, cp2m);
-        moved(g, bmm, nu, +1, cmmpn);
-        moved(g, cpn, nu, +1, cp2n);
-        M3<T> t, end;
-        // 2x1 ahead: U_nu(x) U_mu(x+nu) U_mu(x+nu+mu) U_nu(x+2mu)^dag [U_mu(x+mu)^dag]
-        t = mul(up, L.at(g, cpnpm, mu));
-        mac_nd(t, L.at(g, cp2m, nu), ahead);
-        // 2x1 behind: U_mu(x-mu)^dag U_nu(x-mu) U_mu(x-mu+nu) U_mu(x+nu) [U_nu(x+mu)^dag]
-        t = mul_dn(umu_xmm, L.at(g, bmm, nu));
-        t = mul(t, L.at(g, cmmpn, mu));
-        end = mul(t, umu_xpn);
-        // 1x2: U_nu(x) U_nu(x+nu) U_mu(x+2nu) U_nu(x+mu+nu)^dag [U_nu(x+mu)^dag]
-        t = mul(unu_x, L.at(g, cpn, nu));
-        t = mul(t, L.at(g, cp2n, mu));
-        mac_nd(t, L.at(g, cpnpm, nu), end);
-        mac_nd(end, unu_xpm, Cr);
-      }
+      M3<T> t, end;
+      // 2x1 ahead: U_nu(x) U_mu(x+nu) U_mu(x+nu+mu) U_nu(x+2mu)^dag [U_mu(x+mu)^dag]
+      t = mul(up, L.load_off(mu, x.even(n1 + m1)));
+      x = opaque_site(x, t);
+      mac_nd(t, L.load_off(nu, x.even(m2)), ahead);
+      // 2x1 behind: U_mu(x-mu)^dag U_nu(x-mu) U_mu(x-mu+nu) U_mu(x+nu) [U_nu(x+mu)^dag]
+      t = mul_dn(umu_xmm, L.load_off(nu, x.odd(m_1)));
+      t = mul(t, L.load_off(mu, x.even(m_1 + n1)));
+      end = mul(t, umu_xpn);
+      x = opaque_site(x, end);
+      // 1x2: U_nu(x) U_nu(x+nu) U_mu(x+2nu) U_nu(x+mu+nu)^dag [U_nu(x+mu)^dag]
+      t = mul(unu_x, L.load_off(nu, x.odd(n1)));
+      t = mul(t, L.load_off(mu, x.even(n2)));
+      mac_nd(t, L.load_off(nu, x.even(m1 + n1)), end);
+      mac_nd(end, unu_xpm, Cr);
     }
     {  // -nu
-      int b[4] = {c[0], c[1], c[2], c[3]}, bmm[4] = {cmm[0], cmm[1], cmm[2], cmm[3]};
-      opaque_coords(b);
-      opaque_coords(bmm);
-      int cmn[4], cmnpm[4];
-      moved(g, b, nu, -1, cmn);
-      moved(g, cmn, mu, +1, cmnpm);
-      const M3<T> unu_xmn = L.at(g, cmn, nu);      // U_nu(x-nu)
-      const M3<T> umu_xmn = L.at(g, cmn, mu);      // U_mu(x-nu)
-      const M3<T> unu_xmnpm = L.at(g, cmnpm, nu);  // U_nu(x-nu+mu)
-      const M3<T> dn = mul_dn(unu_xmn, umu_xmn);   // U_nu(x-nu)^dag U_mu(x-nu)
+      Around<T> x = opaque_site(x0, Cr);
+      const int n_1 = move_by<T>(g, c, nu, -1), n_2 = move_by<T>(g, c, nu, -2);
+      const M3<T> unu_xmn = L.load_off(nu, x.odd(n_1));           // U_nu(x-nu)
+      const M3<T> umu_xmn = L.load_off(mu, x.odd(n_1));           // U_mu(x-nu)
+      const M3<T> unu_xmnpm = L.load_off(nu, x.even(n_1 + m1));   // U_nu(x-nu+mu)
+      M3<T> dn = mul_dn(unu_xmn, umu_xmn);                        // U_nu(x-nu)^dag U_mu(x-nu)
+      x = opaque_site(x, dn);
       mac(dn, unu_xmnpm, Cp);
-      if (OI) {
-        int cmnp2m[4], cmmmn[4], cm2n[4], cm2npm[4];
-        moved(g, cmnpm, mu, +1, cmnp2m);
-        moved(g, bmm, nu, -1, cmmmn);
-        moved(g, cmn, nu, -1, cm2n);
-        moved(g, cm2n, mu, +1, cm2npm);
-        M3<T> t, end;
-        // 2x1 ahead: U_nu(x-nu)^dag U_mu(x-nu) U_mu(x-nu+mu) U_nu(x-nu+2mu) [U_mu(x+mu)^dag]
-        t = mul(dn, L.at(g, cmnpm, mu));
-        mac(t, L.at(g, cmnp2m, nu), ahead);
-        // 2x1 behind: U_mu(x-mu)^dag U_nu(x-mu-nu)^dag U_mu(x-mu-nu) U_mu(x-nu) [U_nu(x-nu+mu)]
-        t = dag(mul(L.at(g, cmmmn, nu), umu_xmm));
-        t = mul(t, L.at(g, cmmmn, mu));
-        end = mul(t, umu_xmn);
-        // 1x2: U_nu(x-nu)^dag U_nu(x-2nu)^dag U_mu(x-2nu) U_nu(x-2nu+mu) [U_nu(x-nu+mu)]
-        t = dag(mul(L.at(g, cm2n, nu), unu_xmn));
-        t = mul(t, L.at(g, cm2n, mu));
-        mac(t, L.at(g, cm2npm, nu), end);
-        mac(end, unu_xmnpm, Cr);
-      }
+      M3<T> t, end;
+      // 2x1 ahead: U_nu(x-nu)^dag U_mu(x-nu) U_mu(x-nu+mu) U_nu(x-nu+2mu) [U_mu(x+mu)^dag]
+      t = mul(dn, L.load_off(mu, x.even(n_1 + m1)));
+      x = opaque_site(x, t);
+      mac(t, L.load_off(nu, x.odd(n_1 + m2)), ahead);
+      // 2x1 behind: U_mu(x-mu)^dag U_nu(x-mu-nu)^dag U_mu(x-mu-nu) U_mu(x-nu) [U_nu(x-nu+mu)]
+      t = dag(mul(L.load_off(nu, x.even(m_1 + n_1)), umu_xmm));
+      t = mul(t, L.load_off(mu, x.even(m_1 + n_1)));
+      end = mul(t, umu_xmn);
+      x = opaque_site(x, end);
+      // 1x2: U_nu(x-nu)^dag U_nu(x-2nu)^dag U_mu(x-2nu) U_nu(x-2nu+mu) [U_nu(x-nu+mu)]
+      t = dag(mul(L.load_off(nu, x.even(n_2)), unu_xmn));
+      t = mul(t, L.load_off(mu, x.even(n_2)));
+      mac(t, L.load_off(nu, x.odd(n_2 + m1)), end);
+      mac(end, unu_xmnpm, Cr);
     }
   }
-  if (OI) mac_nd(ahead, L.at(g, cpm, mu), Cr);  // ... U_mu(x+mu)^dag
+  mac_nd(ahead, L.load_off(mu, x0.odd(m1)), Cr);  // ... U_mu(x+mu)^dag
 }
 
 }  // namespace mcg

@@ -9,7 +9,7 @@ namespace mcg {
 // CS = 1: also store the staple sums Cp (and Cr, OI) of every link in Cst, as two link fields
 // [Cp | Cr], for the adjoint's first pass
 template <typename T, bool OI, int CS = 0>
-__global__ __launch_bounds__(128) void k_smear(Geom g, const V2<T> *__restrict__ U,
+__global__ __launch_bounds__(128, sizeof(T) == 4 ? (OI ? 2 : 3) : 1) void k_smear(Geom g, const V2<T> *__restrict__ U,
                                                V2<T> *__restrict__ out, T rho, T wp, T wr,
                                                V2<T> *__restrict__ Cst = nullptr) {
   // one block per (tile, direction, parity), the tiles as gather_site lays them out; the eight blocks
@@ -21,10 +21,8 @@ __global__ __launch_bounds__(128) void k_smear(Geom g, const V2<T> *__restrict__
   if (h < 0) return;
   const int mu = (w & 7) >> 1, par = w & 1;
   const Links<T> L{const_cast<V2<T> *>(U), g.Vh};
-  int c[4];
-  coords_of(g, par, h, c);
   M3<T> Cp, Cr;
-  staples<T, OI>(g, L, c, mu, Cp, Cr);
+  staples<T, OI>(g, L, par, h, mu, Cp, Cr);
   if constexpr (CS != 0) {
     Links<T>{Cst, g.Vh}.store(mu, par, h, Cp);
     if (OI) Links<T>{Cst + (size_t)72 * g.Vh, g.Vh}.store(mu, par, h, Cr);
