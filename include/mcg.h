@@ -245,7 +245,11 @@ mcg_status mcg_precondition_batch(mcg_ctx *ctx, int32_t B, const mcg_field *U, d
  * precision and that form, and returns it (best_variant,
  * ms_per_halfsweep[MCG_NUM_VARIANTS] nullable, host: the medians).  The variant fixes the
  * block decomposition of every fixing kernel, hence the order of the FP64
- * partial sums: results at one variant are deterministic. */
+ * partial sums: results at one variant are deterministic.  Launches too small
+ * to fill the device (up to 65,536 sites over a batch with FP32 links, 32,768
+ * with FP64) use another form of the kernel, one wave per link, with the same
+ * results, unless mcg_set_variant has been called for that precision and form;
+ * mcg_tune_batch times that form as the schedule in use. */
 #define MCG_NUM_VARIANTS 6
 mcg_status mcg_autotune(mcg_ctx *ctx, const mcg_field *U, int32_t *best_variant,
                         double *ms_per_halfsweep, void *stream);

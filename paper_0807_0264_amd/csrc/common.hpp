@@ -310,6 +310,30 @@ __device__ __forceinline__ int xcd_range(int i, int n) {
   const int x = i & 7, q = n >> 3, r = n & 7;
   return x * q + (x < r ? x : r) + (i >> 3);
 }
+// One block's value handed to another block of the same launch, without a fence (which would write back
+// and invalidate the L2 of every block's XCD): stores and loads of device scope go past the L2s to the
+// memory that all XCDs share, so a store that has been waited for is seen by every later load of
+// device scope.
+__device__ __forceinline__ void store_device(double *p, double v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#else
+  *p = v;
+#endif
+}
+__device__ __forceinline__ double load_device(const double *p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#else
+  return *p;
+#endif
+}
+// every memory access of this wave so far has been carried out
+__device__ __forceinline__ void wait_memory() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#endif
+}
 // a value that is the same in all lanes of a wave, held in a scalar register
 __device__ __forceinline__ int wave_uniform(int x) {
 #if defined(__HIP_DEVICE_COMPILE__)

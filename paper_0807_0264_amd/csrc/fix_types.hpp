@@ -10,7 +10,8 @@
 namespace mcg {
 
 // Device-resident state of one field's fixing loop.  Written only by the
-// single-block bookkeeping kernels (init / reset / check / final).
+// single-block bookkeeping kernels (init / reset / check / final) and by the
+// last block of an odd half-sweep that takes the check along.
 struct FixState {
   double R_prev;   // R before the current sweep
   double R_last;   // R after the last sweep
@@ -25,6 +26,8 @@ struct FixState {
   int32_t stop_every;   // the stop test only after sweeps whose global number is a multiple of it
   int32_t start_sweep;  // global number of the sweep before this call's first
   int32_t kfold;        // sweeps whose transforms have been folded into G (k - kfold still in the ring)
+  uint64_t arrived;     // blocks of the current odd half-sweep that have left their partial sums
+                        // (k_halfsweep_wide, whose last block does the bookkeeping)
 };
 
 constexpr int MAX_SLABS = 16;

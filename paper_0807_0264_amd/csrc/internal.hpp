@@ -28,6 +28,14 @@ template <typename T>
 hipError_t launch_halfsweep(int variant, bool c12, const void *D, int B, int blocks, int par, double omega,
                             bool withR, bool gated, hipStream_t s, int slab = -1, int hits = 1, int exact = 0,
                             int rev = 0, int gslot = -1, int pend = -1, int keep = 0);
+// the same for a launch too small to fill the device (two-row form, one hit, not exact): one wave per
+// link of 64 sites; the descriptors use blocks of 64 (WIDE_VARIANT).  book (odd half-sweeps with R, at
+// most WIDE_BOOK blocks per field): the stop test of the sweep too, instead of launch_book(BOOK_CHECK)
+constexpr int WIDE_VARIANT = 0;
+constexpr int WIDE_BOOK = 192;
+template <typename T>
+hipError_t launch_halfsweep_wide(const void *D, int B, int blocks, int par, double omega, bool withR, bool gated,
+                                 hipStream_t s, int slab, int rev, int gslot, int pend, int keep, bool book);
 // fold the ring's transforms into G (nfix: the count for fields without a FixState)
 template <typename T>
 hipError_t launch_fold(int bs, bool c12, const void *D, int B, int blocks, int nfix, hipStream_t s);

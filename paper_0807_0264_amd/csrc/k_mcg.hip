@@ -117,6 +117,25 @@ hipError_t launch_halfsweep(int variant, bool c12, const void *D, int B, int blo
 }
 
 template <typename T>
+hipError_t launch_halfsweep_wide(const void *D, int B, int blocks, int par, double omega, bool withR, bool gated,
+                                 hipStream_t s, int slab, int rev, int gslot, int pend, int keep, bool book) {
+  const LatDesc<T> *dd = (const LatDesc<T> *)D;
+  if (book && !withR) return hipErrorInvalidValue;
+  if (keep && (pend < 0 || withR || (gslot >= 0 && gslot != pend))) return hipErrorInvalidValue;
+#define MCG_HW(WR, MODE) \
+  k_halfsweep_wide<T, WR, MODE><<<blocks, 512, 0, s>>>(dd, B, par, (T)omega, gated ? 1 : 0, slab, rev, gslot, pend, book ? 1 : 0)
+  if (keep) {
+    MCG_HW(false, KEEP);
+  } else if (pend >= 0) {
+    if (withR) MCG_HW(true, PEND); else MCG_HW(false, PEND);
+  } else {
+    if (withR) MCG_HW(true, PLAIN); else MCG_HW(false, PLAIN);
+  }
+#undef MCG_HW
+  return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_rederive(int bs, bool c12, const void *D, int B, int blocks, bool gated, hipStream_t s) {
   const LatDesc<T> *dd = (const LatDesc<T> *)D;
   if (c12) {
@@ -181,6 +200,8 @@ hipError_t launch_gauge_form(const Geom &g, const double *src, double *dst, bool
 #define MCG_INST(T)                                                                                  \
   template hipError_t launch_halfsweep<T>(int, bool, const void *, int, int, int, double, bool, bool,  \
                                           hipStream_t, int, int, int, int, int, int, int);           \
+  template hipError_t launch_halfsweep_wide<T>(const void *, int, int, int, double, bool, bool, hipStream_t, int, int, \
+                                               int, int, int, bool);                                  \
   template hipError_t launch_fold<T>(int, bool, const void *, int, int, int, hipStream_t);            \
   template hipError_t launch_rederive<T>(int, bool, const void *, int, int, bool, hipStream_t);       \
   template hipError_t launch_reunit<T>(int, bool, const void *, int, int, bool, hipStream_t);         \

@@ -54,9 +54,10 @@ struct mcg_ctx {
   size_t scratch_used = 0;
   int stop_every = 1;  // stop test only after sweeps numbered by multiples of this (MCG_OPT_STOP_EVERY)
   int variant[2][2] = {{2, 2}, {2, 2}};  // half-sweep variant per [precision][two-row form]
+  bool variant_set[2][2] = {};  // set by the caller (mcg_set_variant)
   // launch variant and schedule chosen by mcg_tune_batch, per batch shape (tune_key); used by the
   // fixes of that shape until an explicit variant or schedule option is set
-  std::map<std::string, mcg_tune_choice> tuned;
+  std::map<std::string, std::pair<mcg_tune_choice, bool>> tuned;  // the bool: one wave per link
   double *noalloc = nullptr;  // this device's address of the allocation-free entry point's scratch
   std::string noalloc_err;    // why it is missing, if it is
 };
@@ -318,9 +319,23 @@ static int tile_order(int order, int par) { return order == 0 ? 0 : (order == 2 
 // this batch shape (precision, storage form, transform ring, update variant, the fields' extents in
 // order), else the context's variant and options.  Re-linearisation hits and exact steps run with
 // 256-thread blocks (variant 2).  Every choice gives the same bits.
+// Where the caller set no variant (mcg_set_variant), a launch of few sites runs one wave per link
+// (k_halfsweep_wide) instead, and mcg_tune_batch times that form as the schedule in use.
 struct Sched {
   int variant, order, paired, nslab;
+  bool wide = false;
 };
+// Blocks of 64 sites (over all fields of the launch) up to which one wave per link is the faster form:
+// FP32 (six waves per SIMD) 18.0 us per sweep against 19.4-21.0 at 512 blocks (16^4) and 28.3 against
+// 22.9-24.6 at 1024; FP64 (one block per CU: 91 KB of LDS) 17.7 against 22.9-25.8 at 162 blocks (12^4) and
+// 32.7 against 26.2-28.5 at 512, where a second round of blocks has begun.
+constexpr int WIDE_BLOCKS_F32 = 512, WIDE_BLOCKS_F64 = 256;
+bool wide_launch(const mcg_ctx *ctx, int B, const mcg_field *U) {
+  if (!ctx->c12 || ctx->hits > 1 || ctx->exact || ctx->variant_set[U[0].prec][1]) return false;
+  int64_t n = 0;
+  for (int b = 0; b < B; b++) n += nblocks(geom_of(U[b].d), 64);
+  return n <= (U[0].prec == MCG_F32 ? WIDE_BLOCKS_F32 : WIDE_BLOCKS_F64);
+}
 std::string tune_key(const mcg_ctx *ctx, int B, const mcg_field *U) {
   std::string k = std::to_string(U[0].prec) + (ctx->c12 ? "/rows" : "/full") + (ctx->defer_g ? "/ring" : "/G") +
                   "/hits" + std::to_string(ctx->hits) + (ctx->exact ? "/exact" : "");
@@ -333,7 +348,11 @@ std::string tune_key(const mcg_ctx *ctx, int B, const mcg_field *U) {
 Sched schedule_of(const mcg_ctx *ctx, int B, const mcg_field *U) {
   Sched r{ctx->variant[U[0].prec][ctx->c12], ctx->order, ctx->paired, ctx->nslab};
   const auto it = ctx->tuned.find(tune_key(ctx, B, U));
-  if (it != ctx->tuned.end()) r = Sched{it->second.variant, it->second.order, it->second.paired, it->second.slabs};
+  if (it != ctx->tuned.end())
+    r = Sched{it->second.first.variant, it->second.first.order, it->second.first.paired, it->second.first.slabs,
+              it->second.second};
+  else if (wide_launch(ctx, B, U))
+    r.variant = WIDE_VARIANT, r.wide = true;
   if (ctx->hits > 1 || ctx->exact) r.variant = 2;
   return r;
 }
@@ -362,6 +381,8 @@ template <typename T> struct FixRun {
   // the odd one applies it to the links it loads.
   bool paired = false;
   bool hand = false;
+  bool wide = false;  // one wave per link (k_halfsweep_wide) ...
+  bool book = false;  // ... whose odd half-sweeps make the stop test
 
   mcg_status pass(int par, bool wr, int slab) {
     const int blocks = slab < 0 ? total_blocks : grid[slab];
@@ -372,7 +393,10 @@ template <typename T> struct FixRun {
       keep = par == 0 ? 1 : 0;
       pend = C ? (par == 0 ? slot : slot - 1) : 0;
     }
-    if (blocks > 0)
+    if (blocks > 0 && wide)
+      HIPCHK(launch_halfsweep_wide<T>(dD, B, blocks, par, omega, wr, gated, s, slab, tile_order(order, par), slot,
+                                      pend, keep, wr && book));
+    else if (blocks > 0)
       HIPCHK(launch_halfsweep<T>(variant, c12, dD, B, blocks, par, omega, wr, gated, s, slab, hits, exact,
                                  tile_order(order, par), slot, pend, keep));
     return MCG_OK;
@@ -415,7 +439,7 @@ template <typename T> struct FixRun {
       HIPCHK(launch_book<T>(dD, B, BOOK_RESET, s));
     }
     if ((st = halfsweeps(true))) return st;
-    HIPCHK(launch_book<T>(dD, B, BOOK_CHECK, s));
+    if (!(wide && book)) HIPCHK(launch_book<T>(dD, B, BOOK_CHECK, s));
     return advance();
   }
 };
@@ -507,6 +531,8 @@ mcg_status fix_impl(mcg_ctx *ctx, int B, const mcg_field *U, mcg_gauge *G, const
   run.hits = ctx->hits;
   run.exact = ctx->exact ? 1 : 0;
   run.order = sc.order;
+  run.wide = run.book = sc.wide;
+  for (int b = 0; b < B; b++) run.book = run.book && hD[b].npart <= WIDE_BOOK;
   run.C = ring ? gring_sweeps(re) : 0;
   run.paired = sc.paired != 0;
   run.hand = hand;
@@ -1085,7 +1111,8 @@ static mcg_status halfsweep_impl(mcg_ctx *ctx, mcg_field *W, mcg_gauge *G, int p
                                  hipStream_t s, int n = 1, double *ms = nullptr) {
   const Geom g = geom_of(W->d);
   const bool c12 = parity < 0 && ctx->c12;
-  const int variant = (ctx->hits > 1 || ctx->exact) ? 2 : ctx->variant[W->prec][c12],
+  const bool wide = c12 && wide_launch(ctx, 1, W);
+  const int variant = (ctx->hits > 1 || ctx->exact) ? 2 : wide ? WIDE_VARIANT : ctx->variant[W->prec][c12],
             nb = nblocks(g, variant_block(variant));
   mcg_status st;
   if ((st = ensure(ctx, ctx->desc, sizeof(LatDesc<T>))) || (st = ensure_pinned(ctx, sizeof(LatDesc<T>))))
@@ -1115,6 +1142,7 @@ static mcg_status halfsweep_impl(mcg_ctx *ctx, mcg_field *W, mcg_gauge *G, int p
   run.hits = ctx->hits;
   run.exact = ctx->exact ? 1 : 0;
   run.order = ctx->order;
+  run.wide = wide;
   run.C = ring ? GRING_SWEEPS : 0;
   run.paired = ctx->paired != 0;
   run.hand = hand;
@@ -1366,6 +1394,7 @@ static mcg_status tune_impl(mcg_ctx *ctx, int B, const mcg_field *U, mcg_tune_ch
     run.gated = false;
     run.stateful = false;
     run.order = p.order;
+    run.wide = p.wide;
     run.C = ring ? 1 : 0;  // g to ring slots 0 and 1; no fold is timed
     run.paired = p.paired != 0;
     run.hand = hand && p.paired == 2;
@@ -1427,7 +1456,7 @@ static mcg_status tune_impl(mcg_ctx *ctx, int B, const mcg_field *U, mcg_tune_ch
       int ib = -1;
       for (size_t i = 0; i < pts.size(); i++)
         if (pts[i].variant == base.variant && pts[i].order == base.order && pts[i].paired == base.paired &&
-            pts[i].nslab == base.nslab)
+            pts[i].nslab == base.nslab && !base.wide)
           ib = (int)i;
       if (ib < 0) {
         ib = (int)pts.size();
@@ -1444,7 +1473,7 @@ static mcg_status tune_impl(mcg_ctx *ctx, int B, const mcg_field *U, mcg_tune_ch
         c.slabs = pts[i].nslab;
         c.ms_per_sweep = med[i];
         c.ms_default = med[ib];
-        ctx->tuned[tune_key(ctx, B, U)] = c;
+        ctx->tuned[tune_key(ctx, B, U)] = {c, pts[i].wide};
         if (out) *out = c;
       }
     }
@@ -1502,6 +1531,7 @@ mcg_status mcg_set_variant(mcg_ctx *ctx, int32_t prec, int32_t variant) {
   if ((prec != MCG_F64 && prec != MCG_F32) || variant < 0 || variant >= NUM_VARIANTS)
     return fail(ctx, MCG_EINVAL, "bad precision or variant");
   ctx->variant[prec][ctx->c12] = variant;
+  ctx->variant_set[prec][ctx->c12] = true;
   return MCG_OK;
 }
 

@@ -523,6 +523,202 @@ __global__ __launch_bounds__(BS, OCC) void k_halfsweep(const LatDesc<T> *__restr
   }
 }
 
+// the stop test after a sweep whose functional is R (one thread); sv: the state before
+template <typename T>
+__device__ __forceinline__ void book_check(const LatDesc<T> &d, FixState *st, const FixState &sv, double R) {
+  const double dR = R - sv.R_prev;
+  const int k = sv.k + 1;
+  st->k = k;
+  st->dR = dR;
+  st->R_last = R;
+  if (d.traj) d.traj[k] = R;
+  if (dR < sv.tol && (sv.start_sweep + k) % sv.stop_every == 0) {
+    st->done = 1;
+    st->status = 0;
+  } else if (k >= sv.max_k) {
+    st->done = 1;
+    st->status = 1;
+  } else {
+    st->R_prev = R;
+  }
+}
+
+// The half-sweep of a launch too small to fill the device, in the two-row form, for the plain update:
+// one wave per link of 64 sites (eight waves in a block; wave k the forward link of direction k, or the
+// backward one of direction k - 4) instead of all eight links of a site in one lane.  A small
+// launch of k_halfsweep is a single pass of every wave through 2,500 instructions that it has to fetch
+// first; here each wave goes through the instructions of one link.  Every value is formed by the same
+// expressions in the same order: X element by element over the eight links from LDS, one wave per
+// element, then the subgroup steps in every wave; the traces of the written links go through LDS for
+// the one sum per site.  Same results as k_halfsweep, bit for bit.
+// book: the block that is last to leave its partial sum adds them all, in k_book's order, and makes the
+// stop test of the sweep.  That saves a launch of 5 us; the handover costs 2.5 us at 8^4 (32 blocks,
+// 15.6 us per sweep of a fix in all) and grows with the blocks that count one after the other, so from
+// WIDE_BOOK blocks on k_book is launched (162 blocks: 18.3 against 18.6 us; 512: 25.2 against 23.9).
+// Handed over by fences instead, every block would write back its XCD's L2: 17.8 and 36.6 us.
+// Sweeps of a fix, FP32 (k_halfsweep with 256-thread blocks and k_book): 4^4 14.7 (18.9) us, 8^4 15.6
+// (22.9), 12^4 18.3 (24.2); FP64: 8^4 17.3 (25.8), 12^4 20.7 (28.5).
+template <typename T, bool WR, int MODE>
+__global__ __launch_bounds__(512) void k_halfsweep_wide(const LatDesc<T> *__restrict__ D, int B, int par, T omega,
+                                                        int gated, int slab, int rev, int gslot, int pend, int book) {
+  constexpr bool keep = MODE == KEEP;
+  __shared__ V2<T> mat[8][9][64];  // each link as it enters X
+  __shared__ V2<T> tr[8][64];      // its trace; after X, the traces of the written links
+  __shared__ V2<T> xs[9][64];
+  int lb;
+  const int b = block_of(D, B, slab, rev, lb);
+  const LatDesc<T> d = D[b];
+  const int done = gated ? d.st->done : 0;  // waited for after the loads below are on their way
+  const int lane = (int)threadIdx.x & 63, link = wave_uniform((int)threadIdx.x >> 6), mu = link & 3;
+  const bool back = link >= 4;
+  const int h = lb * 64 + lane;
+  const bool live = h < d.g.Vh;
+  const Links12<T> W{d.W, d.g.Vh};
+  unsigned o = 0;
+  M3<T> m = m_zero<T>();
+  if (live) {
+    // the half indices of x - mu and x + mu: a step along y, z or t is a stride (Lx is even), a step
+    // along x what x >> 1 moves
+    int c[4];
+    coords_of(d.g, par, h, c);
+    const int x = mu == 0 ? c[0] : mu == 1 ? c[1] : mu == 2 ? c[2] : c[3];
+    const int n = mu == 0 ? d.g.L[0] : mu == 1 ? d.g.L[1] : mu == 2 ? d.g.L[2] : d.g.L[3];
+    const int st = mu == 0 ? 1 : mu == 1 ? d.g.hx : d.g.hx * d.g.L[1] * (mu == 2 ? 1 : d.g.L[2]);
+    const int xb = x == 0 ? n - 1 : x - 1, xf = x == n - 1 ? 0 : x + 1;
+    const int hb = h + (mu == 0 ? (xb >> 1) - (x >> 1) : (xb - x) * st);
+    const int hf = h + (mu == 0 ? (xf >> 1) - (x >> 1) : (xf - x) * st);
+    o = back ? W.off(1 - par, hb) : W.off(par, h);
+    m = W.load_rows(mu, o);
+    if constexpr (MODE == PEND) {
+      M3<T> g = ring_g<T>(d.gring + (size_t)pend * 6 * d.g.Vh, d.g.Vh, back ? hb : hf);
+      third_row_fixed(g);
+      if (!back) {
+        m = mul_nd_fixed_rows(m, g);
+      } else {
+        M3<T> q = m;
+        third_row_fixed(q);
+        m = mul_fixed_rows(g, q);
+      }
+    }
+  }
+  if (done) return;  // uniform over the block
+  {
+    M3<T> f = m;
+    third_row(f);
+    const cx<T> t = trace(f);
+#pragma unroll
+    for (int k = 0; k < 9; k++) {
+      V2<T> v;
+      v.x = f.e[k].re;
+      v.y = f.e[k].im;
+      mat[link][k][lane] = v;
+    }
+    V2<T> v;
+    v.x = t.re;
+    v.y = t.im;
+    tr[link][lane] = v;
+  }
+  __syncthreads();
+  for (int el = link; el < 9; el += 8) {
+    const int dag_el = 3 * (el % 3) + el / 3;  // the backward links enter daggered
+    cx<T> x{T(0), T(0)};
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      const V2<T> tv = tr[k][lane], mv = mat[k][el][lane];
+      x = x + conj(cx<T>{tv.x, tv.y}) * cx<T>{mv.x, mv.y};
+    }
+#pragma unroll
+    for (int k = 4; k < 8; k++) {
+      const V2<T> tv = tr[k][lane], mv = mat[k][dag_el][lane];
+      x = x + cx<T>{tv.x, tv.y} * conj(cx<T>{mv.x, mv.y});
+    }
+    V2<T> v;
+    v.x = x.re;
+    v.y = x.im;
+    xs[el][lane] = v;
+  }
+  __syncthreads();
+  M3<T> X;
+#pragma unroll
+  for (int k = 0; k < 9; k++) {
+    const V2<T> v = xs[k][lane];
+    X.e[k] = cx<T>{v.x, v.y};
+  }
+  const M3<T> g = local_update<T>(X, omega);
+  if (!keep) {
+    M3<T> gr = g;
+    third_row_fixed(gr);
+    opaque_rows(m);  // products shared with third_row's above would change how the compiler fuses those
+    third_row_fixed(m);
+    M3<T> n;
+    if (!back) n = mul(gr, m);
+    else n = mul_nd(m, gr);
+    if (live) W.store_off(mu, o, n);
+    if (WR) {
+      const cx<T> t = trace(n);
+      V2<T> v;
+      v.x = t.re;
+      v.y = t.im;
+      tr[link][lane] = v;  // X has been summed: the traces' first use is over
+    }
+  }
+  const unsigned og = (unsigned)h * (unsigned)sizeof(V2<T>);
+  if (live && link == 0 && (keep || gslot >= 0)) {
+    // rows 0 and 1 of g: into slot pend for the second half of a paired sweep, or into the ring
+    V2<T> *slot = d.gring + (size_t)(keep ? pend : gslot) * 6 * d.g.Vh;
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+      V2<T> v;
+      v.x = g.e[k].re;
+      v.y = g.e[k].im;
+      st_plane(slot + (size_t)k * d.g.Vh, og, v);
+    }
+  }
+  if (live && link == 1 && gslot < 0) {
+    const Gauge12 G{d.G, d.g.Vh};
+    M3<double> gd = m_cvt<double>(g);
+    if constexpr (sizeof(T) == 4) third_row_fixed(gd);
+    G.store(par, h, mul(gd, G.load_fixed(par, h)));
+  }
+  if (WR) {
+    __syncthreads();
+    if (link == 0) {
+      double r = 0.0;
+      if (live) {
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+          const V2<T> v = tr[k][lane];
+          const double re = (double)v.x, im = (double)v.y;
+          r += re * re + im * im;
+        }
+      }
+      const double s = wave_sum(r);
+      if (lane == 0) {
+        if (book) store_device(&d.part[lb], s);
+        else d.part[lb] = s;
+      }
+    }
+    if (book) {
+      __shared__ int last;
+      if (threadIdx.x == 0) {
+        wait_memory();  // the partial sum, stored by this thread, before the count
+        last = atomicAdd((unsigned long long *)&d.st->arrived, 1ull) + 1 == (unsigned long long)d.nblk;
+      }
+      __syncthreads();
+      if (!last) return;
+      wait_memory();
+      FixState *st = d.st;
+      const double v = (int)threadIdx.x < d.npart ? load_device(&d.part[threadIdx.x]) : 0.0;
+      const double s = block_sum<512>(v);  // npart <= 512: the terms and the order of sum_partials<1024>
+      if (threadIdx.x == 0) {
+        const FixState sv = *st;
+        book_check(d, st, sv, s / (9.0 * (double)(4 * d.g.V)));
+        st->arrived = 0;
+      }
+    }
+  }
+}
+
 // W = U^G (FP64 products, rounded once), with per-block sums of |tr W|^2.
 template <typename T, int BS, bool C12>
 __global__ __launch_bounds__(BS) void k_rederive(const LatDesc<T> *__restrict__ D, int B, int gated) {
@@ -708,24 +904,9 @@ __global__ __launch_bounds__(1024) void k_book(const LatDesc<T> *__restrict__ D,
   case BK_RESET:
     st->R_prev = R;
     break;
-  case BK_CHECK: {
-    const double dR = R - sv.R_prev;
-    const int k = sv.k + 1;
-    st->k = k;
-    st->dR = dR;
-    st->R_last = R;
-    if (d.traj) d.traj[k] = R;
-    if (dR < sv.tol && (sv.start_sweep + k) % sv.stop_every == 0) {
-      st->done = 1;
-      st->status = 0;
-    } else if (k >= sv.max_k) {
-      st->done = 1;
-      st->status = 1;
-    } else {
-      st->R_prev = R;
-    }
+  case BK_CHECK:
+    book_check(d, st, sv, R);
     break;
-  }
   case BK_FINAL:
     st->R_final = R;
     break;
