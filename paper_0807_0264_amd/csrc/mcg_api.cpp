@@ -54,7 +54,8 @@ struct mcg_ctx {
   size_t scratch_used = 0;
   int stop_every = 1;  // stop test only after sweeps numbered by multiples of this (MCG_OPT_STOP_EVERY)
   int variant[2][2] = {{2, 2}, {2, 2}};  // half-sweep variant per [precision][two-row form]
-  bool variant_set[2][2] = {};  // set by the caller (mcg_set_variant)
+  enum { DEFAULT, TUNED, SET };
+  int variant_from[2][2] = {};  // who chose it: nobody, mcg_autotune or the caller (mcg_set_variant)
   // launch variant and schedule chosen by mcg_tune_batch, per batch shape (tune_key); used by the
   // fixes of that shape until an explicit variant or schedule option is set
   std::map<std::string, std::pair<mcg_tune_choice, bool>> tuned;  // the bool: one wave per link
@@ -331,7 +332,7 @@ struct Sched {
 // 32.7 against 26.2-28.5 at 512, where a second round of blocks has begun.
 constexpr int WIDE_BLOCKS_F32 = 512, WIDE_BLOCKS_F64 = 256;
 bool wide_launch(const mcg_ctx *ctx, int B, const mcg_field *U) {
-  if (!ctx->c12 || ctx->hits > 1 || ctx->exact || ctx->variant_set[U[0].prec][1]) return false;
+  if (!ctx->c12 || ctx->hits > 1 || ctx->exact || ctx->variant_from[U[0].prec][1] == mcg_ctx::SET) return false;
   int64_t n = 0;
   for (int b = 0; b < B; b++) n += nblocks(geom_of(U[b].d), 64);
   return n <= (U[0].prec == MCG_F32 ? WIDE_BLOCKS_F32 : WIDE_BLOCKS_F64);
@@ -345,8 +346,15 @@ std::string tune_key(const mcg_ctx *ctx, int B, const mcg_field *U) {
   }
   return k;
 }
+// The variant where nobody chose one, two-row form: FP32 128-thread blocks (the benchmark's four lattices
+// 70.5 ms per 150 sweeps, 70.8-71.6 with 256 threads; 16 copies of 16^4 16.0 against 16.3 ms), FP64 64
+// (32^3x64 36.0 against 37.9 ms per 50 sweeps; 8 copies of 16^4 8.8 against 9.1).
+int variant_of(const mcg_ctx *ctx, int prec, bool c12) {
+  if (c12 && ctx->variant_from[prec][1] == mcg_ctx::DEFAULT) return prec == MCG_F32 ? 1 : 0;
+  return ctx->variant[prec][c12];
+}
 Sched schedule_of(const mcg_ctx *ctx, int B, const mcg_field *U) {
-  Sched r{ctx->variant[U[0].prec][ctx->c12], ctx->order, ctx->paired, ctx->nslab};
+  Sched r{variant_of(ctx, U[0].prec, ctx->c12), ctx->order, ctx->paired, ctx->nslab};
   const auto it = ctx->tuned.find(tune_key(ctx, B, U));
   if (it != ctx->tuned.end())
     r = Sched{it->second.first.variant, it->second.first.order, it->second.first.paired, it->second.first.slabs,
@@ -1112,7 +1120,7 @@ static mcg_status halfsweep_impl(mcg_ctx *ctx, mcg_field *W, mcg_gauge *G, int p
   const Geom g = geom_of(W->d);
   const bool c12 = parity < 0 && ctx->c12;
   const bool wide = c12 && wide_launch(ctx, 1, W);
-  const int variant = (ctx->hits > 1 || ctx->exact) ? 2 : wide ? WIDE_VARIANT : ctx->variant[W->prec][c12],
+  const int variant = (ctx->hits > 1 || ctx->exact) ? 2 : wide ? WIDE_VARIANT : variant_of(ctx, W->prec, c12),
             nb = nblocks(g, variant_block(variant));
   mcg_status st;
   if ((st = ensure(ctx, ctx->desc, sizeof(LatDesc<T>))) || (st = ensure_pinned(ctx, sizeof(LatDesc<T>))))
@@ -1315,6 +1323,7 @@ static mcg_status autotune_impl(mcg_ctx *ctx, int B, const mcg_field *U, int32_t
   (void)hipEventDestroy(e1);
   if (rc) return rc;
   ctx->variant[prec][c12] = vbest;
+  ctx->variant_from[prec][c12] = mcg_ctx::TUNED;
   if (best) *best = vbest;
   return MCG_OK;
 }
@@ -1531,7 +1540,7 @@ mcg_status mcg_set_variant(mcg_ctx *ctx, int32_t prec, int32_t variant) {
   if ((prec != MCG_F64 && prec != MCG_F32) || variant < 0 || variant >= NUM_VARIANTS)
     return fail(ctx, MCG_EINVAL, "bad precision or variant");
   ctx->variant[prec][ctx->c12] = variant;
-  ctx->variant_set[prec][ctx->c12] = true;
+  ctx->variant_from[prec][ctx->c12] = mcg_ctx::SET;
   return MCG_OK;
 }
 
