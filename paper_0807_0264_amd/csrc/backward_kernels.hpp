@@ -45,7 +45,7 @@ template <typename T> __device__ __forceinline__ cx<T> trdot(const M3<T> &a, con
 }
 
 // ---------------------------------------------------------- partial sums
-// The loss and the two scalar derivatives from the per-block partials, laid out as the seed's
+// The loss, the two scalar derivatives and the range flag (as 0 or 1) from the per-block partials, laid out as the seed's
 // nb_seed block sums and then, for each of the n steps, 3 nb entries: the (dL/drho, dL/deps) pair
 // of each block, then the rectangle part of dL/deps of each block (zero where no kernel writes it).
 // Block q (0: loss, 1: dL/drho, 2: dL/deps) sums its terms in a fixed order: thread t adds the
@@ -77,7 +77,7 @@ __device__ __forceinline__ double sum_runs(const double *base, int n, int len, l
   return s;
 }
 __global__ __launch_bounds__(1024) void k_reduce_parts(const double *__restrict__ part, int nb_seed, int n, int nb,
-                                                       double *__restrict__ out) {
+                                                       const int *__restrict__ flag, double *__restrict__ out) {
   const int q = blockIdx.x;
   const long long nb3 = 3LL * nb;
   double s;
@@ -86,7 +86,10 @@ __global__ __launch_bounds__(1024) void k_reduce_parts(const double *__restrict_
   else
     s = sum_runs(part + nb_seed, n, 2 * nb, nb3, [nb](int j) { return j < nb ? 2LL * j + 1 : (long long)nb + j; });
   s = block_sum<1024>(s);
-  if (threadIdx.x == 0) out[q] = s;
+  if (threadIdx.x == 0) {
+    out[q] = s;
+    if (q == 0) out[3] = *flag ? 1.0 : 0.0;
+  }
 }
 
 // ------------------------------------------------------------------ seed

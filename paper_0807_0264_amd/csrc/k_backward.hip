@@ -15,8 +15,9 @@ hipError_t launch_loss_seed(const Geom &g, const void *S, const double *G, void 
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_parts(const double *part, int nb_seed, int n, int nb, double *out, hipStream_t s) {
-  k_reduce_parts<<<3, 1024, 0, s>>>(part, nb_seed, n, nb, out);
+hipError_t launch_reduce_parts(const double *part, int nb_seed, int n, int nb, const int *flag, double *out,
+                               hipStream_t s) {
+  k_reduce_parts<<<3, 1024, 0, s>>>(part, nb_seed, n, nb, flag, out);
   return hipGetLastError();
 }
 

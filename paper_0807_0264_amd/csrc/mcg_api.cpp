@@ -42,6 +42,9 @@ struct mcg_ctx {
   DevBuf pc_part, pc_counts;    // mcg_precondition_batch: margin partials and vortex counters
   void *h_pinned = nullptr;
   size_t h_pinned_cap = 0;
+  // host memory that kernels write a call's scalar results into (read after the call's
+  // synchronisation): no copy between the last kernel and the host
+  double *h_res = nullptr;
   bool c12 = true;  // fixing keeps W and G as two rows (MCG_OPT_TWO_ROW)
   int nslab = 1;    // half-sweeps run slab by slab when > 1 (MCG_OPT_SLABS)
   int hits = 1;     // re-linearisation hits per site visit (MCG_OPT_HITS)
@@ -172,6 +175,18 @@ mcg_status ensure_pinned(mcg_ctx *ctx, size_t bytes) {
   return MCG_OK;
 }
 
+constexpr int HOST_RESULTS = 32;
+mcg_status ensure_results(mcg_ctx *ctx) {
+  if (ctx->h_res) return MCG_OK;
+  void *p = nullptr;
+  if (hipHostMalloc(&p, HOST_RESULTS * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(ctx, MCG_ENOMEM, "pinned host allocation of %zu bytes failed", HOST_RESULTS * sizeof(double));
+  }
+  ctx->h_res = (double *)p;
+  return MCG_OK;
+}
+
 bool dims_valid(const mcg_dims &d) {
   int64_t V = 1;
   for (int k = 0; k < 4; k++) {
@@ -253,9 +268,8 @@ mcg_status unitarity(mcg_ctx *ctx, const mcg_field *U, const mcg_gauge *G, doubl
   const mcg_dims &d = U ? U->d : G->d;
   const Geom g = geom_of(d);
   mcg_status st;
-  if ((st = ensure(ctx, ctx->part, sizeof(double) * field_blocks256(g))) || (st = ensure(ctx, ctx->scalars, 64)))
-    return st;
-  double *dv = (double *)ctx->scalars.p + 4;
+  if ((st = ensure(ctx, ctx->part, sizeof(double) * field_blocks256(g))) || (st = ensure_results(ctx))) return st;
+  double *dv = ctx->h_res;
   if (U) {
     if (U->prec == MCG_F64)
       HIPCHK(launch_unitarity<double>(g, U->ptr, 4, (double *)ctx->part.p, dv, s));
@@ -263,11 +277,9 @@ mcg_status unitarity(mcg_ctx *ctx, const mcg_field *U, const mcg_gauge *G, doubl
       HIPCHK(launch_unitarity<float>(g, U->ptr, 4, (double *)ctx->part.p, dv, s));
   }
   if (G) HIPCHK(launch_unitarity<double>(g, G->ptr, 1, (double *)ctx->part.p, dv + 1, s));
-  double h[2] = {0.0, 0.0};
-  HIPCHK(hipMemcpyAsync(h, dv, sizeof h, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  if (devU) *devU = U ? h[0] : 0.0;
-  if (devG) *devG = G ? h[1] : 0.0;
+  if (devU) *devU = U ? dv[0] : 0.0;
+  if (devG) *devG = G ? dv[1] : 0.0;
   return MCG_OK;
 }
 
@@ -746,7 +758,7 @@ static mcg_status precondition_impl(mcg_ctx *ctx, int B, const mcg_field *U, dou
 // then per segment (last first) recompute the c fields from the checkpoint
 // and apply the step adjoints in reverse.  Partial sums of L, dL/drho and
 // dL/deps stay on the device and are reduced there at the end in a fixed
-// order; three scalars and a flag come back.
+// order into host memory, with the range flag.
 template <typename T>
 mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double eps, int n, const mcg_gauge *Gstar,
                          int ckpt_every, mcg_field *gradU, double *loss, double *dRho, double *dEps,
@@ -774,7 +786,7 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
   }
   const int nb_seed = field_blocks256(g), nb_step = adjoint_blocks(g);
   const size_t nparts = (size_t)nb_seed + (size_t)std::max(n, 1) * 3 * nb_step;
-  if ((st = ensure(ctx, ctx->bw_part, sizeof(double) * nparts + 64))) return st;
+  if ((st = ensure(ctx, ctx->bw_part, sizeof(double) * nparts + 64)) || (st = ensure_results(ctx))) return st;
   char *base = (char *)ctx->ckpt.p;
   auto slot = [&](size_t i) { return (void *)(base + i * fb); };
   void *tmp0 = slot(nck + c - 1), *tmp1 = slot(nck + c), *gA = slot(nck + c + 1), *gB = slot(nck + c + 2),
@@ -786,8 +798,7 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
     return stored ? slot((size_t)nck + c + 4 + (size_t)(c - 1) * ncs + (size_t)seg * ncs) : nullptr;
   };
   double *part = (double *)ctx->bw_part.p;
-  double *red = part + nparts;      // the three reduced scalars ...
-  int *flag = (int *)(red + 3);     // ... and the adjoint's range flag, copied back together
+  int *flag = (int *)(part + nparts);  // the adjoint's range flag
   HIPCHK(hipMemsetAsync(flag, 0, sizeof(int), s));
   HIPCHK(hipMemsetAsync(part, 0, sizeof(double) * nparts, s));
 
@@ -835,13 +846,10 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
     }
   }
   if (n == 0) HIPCHK(hipMemcpyAsync(gradU->ptr, gin, fb, hipMemcpyDeviceToDevice, s));
-  HIPCHK(launch_reduce_parts(part, nb_seed, n, nb_step, red, s));
-  double h[4];
-  HIPCHK(hipMemcpyAsync(h, red, 3 * sizeof(double) + sizeof(int), hipMemcpyDeviceToHost, s));
+  HIPCHK(launch_reduce_parts(part, nb_seed, n, nb_step, flag, ctx->h_res, s));
   HIPCHK(hipStreamSynchronize(s));
-  int hflag;
-  std::memcpy(&hflag, &h[3], sizeof(int));
-  if (hflag)
+  const double *h = ctx->h_res;  // the three scalars and the flag
+  if (h[3] != 0.0)
     return fail(ctx, MCG_EINPUT, "a smearing exponent exceeds the range of the adjoint's series "
                                  "(spectral radius of C U^dag above 4)");
   *loss = h[0] / (9.0 * (double)(4 * g.V));
@@ -902,6 +910,7 @@ mcg_status mcg_destroy(mcg_ctx *ctx) {
     for (DevBuf &b : *v)
       if (b.p) (void)hipFree(b.p);
   if (ctx->h_pinned) (void)hipHostFree(ctx->h_pinned);
+  if (ctx->h_res) (void)hipHostFree(ctx->h_res);
   if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
   delete ctx;
   return MCG_OK;
@@ -1040,11 +1049,9 @@ static mcg_status field_scalar(mcg_ctx *ctx, const mcg_field *U, double *out, vo
   if ((st = check_field(ctx, U, "U"))) return st;
   if (!out) return fail(ctx, MCG_EINVAL, "NULL output");
   const Geom g = geom_of(U->d);
-  if ((st = ensure(ctx, ctx->part, sizeof(double) * field_blocks256(g))) ||
-      (st = ensure(ctx, ctx->scalars, 64)))
-    return st;
+  if ((st = ensure(ctx, ctx->part, sizeof(double) * field_blocks256(g))) || (st = ensure_results(ctx))) return st;
   hipStream_t s = (hipStream_t)stream;
-  double *dres = (double *)ctx->scalars.p;
+  double *dres = ctx->h_res;
   if (what == 0) {
     if (U->prec == MCG_F64) HIPCHK(launch_functional<double>(g, U->ptr, (double *)ctx->part.p, dres, s));
     else HIPCHK(launch_functional<float>(g, U->ptr, (double *)ctx->part.p, dres, s));
@@ -1052,8 +1059,8 @@ static mcg_status field_scalar(mcg_ctx *ctx, const mcg_field *U, double *out, vo
     if (U->prec == MCG_F64) HIPCHK(launch_plaquette<double>(g, U->ptr, (double *)ctx->part.p, dres, s));
     else HIPCHK(launch_plaquette<float>(g, U->ptr, (double *)ctx->part.p, dres, s));
   }
-  HIPCHK(hipMemcpyAsync(out, dres, sizeof(double), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  *out = *dres;
   return MCG_OK;
 }
 
@@ -1732,18 +1739,18 @@ mcg_status mcg_center_project(mcg_ctx *ctx, const mcg_field *U, const mcg_gauge 
   if ((st = check_inputs(ctx, U, G, (hipStream_t)stream))) return st;
   const Geom g = geom_of(U->d);
   if ((st = ensure(ctx, ctx->part, sizeof(double) * site_blocks(g))) ||
-      (st = ensure(ctx, ctx->scalars, 64)))
+      (st = min_margin ? ensure_results(ctx) : ensure(ctx, ctx->scalars, 64)))
     return st;
   hipStream_t s = (hipStream_t)stream;
   const double *gp = G ? G->ptr : nullptr;
-  double *dmin = (double *)ctx->scalars.p + 1;
+  double *dmin = min_margin ? ctx->h_res : (double *)ctx->scalars.p + 1;
   if (U->prec == MCG_F64)
     HIPCHK(launch_center_project<double>(g, U->ptr, gp, Z, (double *)ctx->part.p, dmin, s));
   else
     HIPCHK(launch_center_project<float>(g, U->ptr, gp, Z, (double *)ctx->part.p, dmin, s));
   if (min_margin) {
-    HIPCHK(hipMemcpyAsync(min_margin, dmin, sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    *min_margin = *dmin;
   }
   return MCG_OK;
 }
@@ -1785,12 +1792,12 @@ mcg_status mcg_count_vortices(mcg_ctx *ctx, const int8_t *Z, mcg_dims d, int64_t
   if (!Z || !total) return fail(ctx, MCG_EINVAL, "NULL argument");
   if (!dims_valid(d)) return fail(ctx, MCG_EINVAL, "bad extents");
   mcg_status st;
-  if ((st = ensure(ctx, ctx->counts, 12 * sizeof(unsigned long long)))) return st;
+  if ((st = ensure(ctx, ctx->counts, 12 * sizeof(unsigned long long))) || (st = ensure_results(ctx))) return st;
   hipStream_t s = (hipStream_t)stream;
   HIPCHK(hipMemsetAsync(ctx->counts.p, 0, 12 * sizeof(unsigned long long), s));
   HIPCHK(launch_count_vortices(geom_of(d), Z, (unsigned long long *)ctx->counts.p, s));
-  unsigned long long h[12];
-  HIPCHK(hipMemcpyAsync(h, ctx->counts.p, sizeof h, hipMemcpyDeviceToHost, s));
+  const unsigned long long *h = (const unsigned long long *)ctx->h_res;
+  HIPCHK(hipMemcpyAsync(ctx->h_res, ctx->counts.p, 12 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   int64_t tot = 0;
   for (int p = 0; p < 6; p++) {
