@@ -345,7 +345,7 @@ __device__ __forceinline__ int wave_uniform(int x) {
 
 // Tiles of the gather kernels (smearing and its adjoint): a tile is TL (128) half-sites of one t-slice
 // (S = Vh / Lt half-sites per slice, ceil(S / TL) tiles each).  Tiles come in groups of up to
-// eight consecutive t-slices, and inside a group the slice index runs fastest, so the tiles that
+// TG (eight) consecutive t-slices, and inside a group the slice index runs fastest, so the tiles that
 // hold a site's t-neighbours are a few tiles away, not a whole slice (at 32^3x64 a slice of links
 // is larger than an XCD's L2).  gather_site maps (tile, lane) to the half-site index, or -1 for the
 // idle lanes of a slice's last tile; a bijection of [0, gather_tiles) x [0, TL) onto the
@@ -353,11 +353,11 @@ __device__ __forceinline__ int wave_uniform(int x) {
 template <int TL = 128> __host__ __device__ inline int gather_tiles(const Geom &g) {
   return g.L[3] * ((g.Vh / g.L[3] + TL - 1) / TL);
 }
-template <int TL = 128> __device__ __forceinline__ int gather_site(const Geom &g, int tile, int lane) {
-  const int S = g.Vh / g.L[3], span = 8 * ((S + TL - 1) / TL);
+template <int TL = 128, int TG = 8> __device__ __forceinline__ int gather_site(const Geom &g, int tile, int lane) {
+  const int S = g.Vh / g.L[3], span = TG * ((S + TL - 1) / TL);
   const int gi = tile / span, rem = tile - gi * span;
-  const int bt = g.L[3] - 8 * gi < 8 ? g.L[3] - 8 * gi : 8;
-  const int ch = rem / bt, t = 8 * gi + (rem - ch * bt);
+  const int bt = g.L[3] - TG * gi < TG ? g.L[3] - TG * gi : TG;
+  const int ch = rem / bt, t = TG * gi + (rem - ch * bt);
   const int s = ch * TL + lane;
   return s < S ? t * S + s : -1;
 }

@@ -19,8 +19,9 @@ hipError_t launch_smear_step(const Geom &g, const void *U, void *out, double rho
   V2<T> *o = (V2<T> *)out, *cs = (V2<T> *)Cst;
   const T r = (T)rho, p = (T)wp, q = (T)wr;
   if (eps == 1.0) {
-    if (cs) k_smear<T, false, 1><<<grid, 128, 0, s>>>(g, u, o, r, p, q, cs);
-    else k_smear<T, false><<<grid, 128, 0, s>>>(g, u, o, r, p, q);
+    const int blocks = 2 * gather_tiles<64>(g);
+    if (cs) k_smear_stout<T, 1><<<blocks, 256, 0, s>>>(g, u, o, r, p, cs);
+    else k_smear_stout<T><<<blocks, 256, 0, s>>>(g, u, o, r, p);
   } else {
     if (cs) k_smear<T, true, 1><<<grid, 128, 0, s>>>(g, u, o, r, p, q, cs);
     else k_smear<T, true><<<grid, 128, 0, s>>>(g, u, o, r, p, q);
