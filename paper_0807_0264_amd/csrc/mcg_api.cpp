@@ -358,15 +358,24 @@ std::string tune_key(const mcg_ctx *ctx, int B, const mcg_field *U) {
   }
   return k;
 }
-// The variant where nobody chose one, two-row form: FP32 128-thread blocks (the benchmark's four lattices
-// 70.5 ms per 150 sweeps, 70.8-71.6 with 256 threads; 16 copies of 16^4 16.0 against 16.3 ms), FP64 64
-// (32^3x64 36.0 against 37.9 ms per 50 sweeps; 8 copies of 16^4 8.8 against 9.1).
-int variant_of(const mcg_ctx *ctx, int prec, bool c12) {
-  if (c12 && ctx->variant_from[prec][1] == mcg_ctx::DEFAULT) return prec == MCG_F32 ? 1 : 0;
+// The variant where nobody chose one, two-row form.  FP64: 64-thread blocks (60 sweeps of 14^4 1.80 against
+// 1.91 ms with 256 threads, 16^3x20 2.16 against 2.22; 50 of 32^3x64 36.0 against 37.9), except between
+// 120,000 and 600,000 sites (16^3x32 2.95 against 2.91 ms per 60, 20^3x40 the same).  FP32: 128 from
+// 600,000 sites in the launch on (the benchmark's four lattices 70.5 against 70.8-71.6 ms per 150 sweeps,
+// 16 copies of 16^4 16.0 against 16.3), 256 below (16^3x20 1.64 against 1.78 ms per 60 with 128, 20^3x40
+// 3.39 against 3.42).
+int variant_of(const mcg_ctx *ctx, int B, const mcg_field *U, bool c12) {
+  const int prec = U[0].prec;
+  if (c12 && ctx->variant_from[prec][1] == mcg_ctx::DEFAULT) {
+    int64_t V = 0;
+    for (int b = 0; b < B; b++) V += geom_of(U[b].d).V;
+    if (prec == MCG_F64 && (V < 120000 || V >= 600000)) return 0;
+    if (prec == MCG_F32 && V >= 600000) return 1;
+  }
   return ctx->variant[prec][c12];
 }
 Sched schedule_of(const mcg_ctx *ctx, int B, const mcg_field *U) {
-  Sched r{variant_of(ctx, U[0].prec, ctx->c12), ctx->order, ctx->paired, ctx->nslab};
+  Sched r{variant_of(ctx, B, U, ctx->c12), ctx->order, ctx->paired, ctx->nslab};
   const auto it = ctx->tuned.find(tune_key(ctx, B, U));
   if (it != ctx->tuned.end())
     r = Sched{it->second.first.variant, it->second.first.order, it->second.first.paired, it->second.first.slabs,
@@ -1127,7 +1136,7 @@ static mcg_status halfsweep_impl(mcg_ctx *ctx, mcg_field *W, mcg_gauge *G, int p
   const Geom g = geom_of(W->d);
   const bool c12 = parity < 0 && ctx->c12;
   const bool wide = c12 && wide_launch(ctx, 1, W);
-  const int variant = (ctx->hits > 1 || ctx->exact) ? 2 : wide ? WIDE_VARIANT : variant_of(ctx, W->prec, c12),
+  const int variant = (ctx->hits > 1 || ctx->exact) ? 2 : wide ? WIDE_VARIANT : variant_of(ctx, 1, W, c12),
             nb = nblocks(g, variant_block(variant));
   mcg_status st;
   if ((st = ensure(ctx, ctx->desc, sizeof(LatDesc<T>))) || (st = ensure_pinned(ctx, sizeof(LatDesc<T>))))
