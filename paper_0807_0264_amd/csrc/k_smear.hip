@@ -23,8 +23,8 @@ hipError_t launch_smear_step(const Geom &g, const void *U, void *out, double rho
     if (cs) k_smear_stout<T, 1><<<blocks, 256, 0, s>>>(g, u, o, r, p, cs);
     else k_smear_stout<T><<<blocks, 256, 0, s>>>(g, u, o, r, p);
   } else {
-    if (cs) k_smear<T, true, 1><<<grid, 128, 0, s>>>(g, u, o, r, p, q, cs);
-    else k_smear<T, true><<<grid, 128, 0, s>>>(g, u, o, r, p, q);
+    if (cs) k_smear<T, 1><<<grid, 128, 0, s>>>(g, u, o, r, p, q, cs);
+    else k_smear<T><<<grid, 128, 0, s>>>(g, u, o, r, p, q);
   }
   return hipGetLastError();
 }

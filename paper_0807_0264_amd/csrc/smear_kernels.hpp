@@ -6,10 +6,10 @@
 
 namespace mcg {
 
-// CS = 1: also store the staple sums Cp (and Cr, OI) of every link in Cst, as two link fields
-// [Cp | Cr], for the adjoint's first pass
-template <typename T, bool OI, int CS = 0>
-__global__ __launch_bounds__(128, sizeof(T) == 4 ? (OI ? 2 : 3) : 1) void k_smear(Geom g, const V2<T> *__restrict__ U,
+// Over-improved stout, a thread per link.  CS = 1: also store the staple sums Cp and Cr of every link
+// in Cst, as two link fields [Cp | Cr], for the adjoint's first pass
+template <typename T, int CS = 0>
+__global__ __launch_bounds__(128, sizeof(T) == 4 ? 2 : 1) void k_smear(Geom g, const V2<T> *__restrict__ U,
                                                V2<T> *__restrict__ out, T rho, T wp, T wr,
                                                V2<T> *__restrict__ Cst = nullptr) {
   // one block per (tile, direction, parity), the tiles as gather_site lays them out; the eight blocks
@@ -22,17 +22,14 @@ __global__ __launch_bounds__(128, sizeof(T) == 4 ? (OI ? 2 : 3) : 1) void k_smea
   const int mu = (w & 7) >> 1, par = w & 1;
   const Links<T> L{const_cast<V2<T> *>(U), g.Vh};
   M3<T> Cp, Cr;
-  staples<T, OI>(g, L, par, h, mu, Cp, Cr);
+  staples<T, true>(g, L, par, h, mu, Cp, Cr);
   if constexpr (CS != 0) {
     Links<T>{Cst, g.Vh}.store(mu, par, h, Cp);
-    if (OI) Links<T>{Cst + (size_t)72 * g.Vh, g.Vh}.store(mu, par, h, Cr);
+    Links<T>{Cst + (size_t)72 * g.Vh, g.Vh}.store(mu, par, h, Cr);
   }
   M3<T> C;
 #pragma unroll
-  for (int k = 0; k < 9; k++) {
-    C.e[k] = rho * (wp * Cp.e[k]);
-    if (OI) C.e[k] = rho * (wp * Cp.e[k] + wr * Cr.e[k]);
-  }
+  for (int k = 0; k < 9; k++) C.e[k] = rho * (wp * Cp.e[k] + wr * Cr.e[k]);
   const M3<T> u = L.load(mu, par, h);
   const M3<T> E = exp_su3(ta(mul_nd(C, u)));
   Links<T>{out, g.Vh}.store(mu, par, h, mul(E, u));
@@ -41,9 +38,9 @@ __global__ __launch_bounds__(128, sizeof(T) == 4 ? (OI ? 2 : 3) : 1) void k_smea
 // Stout: one block per 64 half-sites of one parity, wave mu the links of direction mu.  Waves mu and
 // nu = mu ^ j take the direction nu and mu of their plane together and read U_nu(x) and U_nu(x+mu) from each
 // other through LDS, so that a link takes 13 matrices from the caches instead of 19 (11.5 GB per
-// 32^3x64 FP32 step, 14 TB/s, was what the step had waited for).  FP32 runs four waves per SIMD (two
-// registers spilled), and tiles in groups of four t-slices, the 64-site tiles of eight being more than an
-// XCD's L2 holds.  CS as in k_smear; the sums in the order of staples<T, false>.
+// 32^3x64 FP32 step, 14 TB/s, was what the step had waited for).  FP32 runs four waves per SIMD (126
+// registers), and tiles in groups of four t-slices, the 64-site tiles of eight being more than an
+// XCD's L2 holds.  CS = 1: also store Cp in Cst; the sums in the order of staples<T, false>.
 // 32^3x64 FP32, per step: 0.802 ms with a wave per link and 19 loads, 0.767 with the exchange at three
 // waves per SIMD, 0.747 at four, 0.713 with the groups of four (of two: 0.744): 76 % of the VALU issue
 // rate.  FP64, 20^3x40 and 16^4: 0.136 -> 0.123 ms on average.
