@@ -440,7 +440,13 @@ mcg_status mcg_vortex_field(mcg_ctx *ctx, const mcg_field *U, const mcg_gauge *G
  * along the axis with steps left whose (steps taken + 1/2) / |v_axis| is
  * smallest, the lower axis on a tie.  Requires 1 <= tmax <= L[3],
  * 0 < |v|_1 <= 24 with |v_j| <= 8, and rmax * max_j |v_j| <= min(L[0], L[1],
- * L[2]); sums in FP64, deterministic.  Synchronises the stream. */
+ * L[2]); sums in FP64, deterministic.  Synchronises the stream.
+ * Where every time link is unitary to rounding (each entry of U_3 U_3^dagger - 1
+ * below 2.4e-7 with FP32 links, 2.5e-15 with FP64) the loops are formed in the
+ * temporal gauge of the links' unitary parts, which leaves out at most T times
+ * that of W(R, T) if all time links are off by the same scale, and what does
+ * not average out over the sites otherwise; any other links are multiplied
+ * out as they are, which takes several times as long. */
 mcg_status mcg_wilson_loops(mcg_ctx *ctx, const mcg_field *U, int32_t nvec, const int32_t *vec,
                             int32_t rmax, int32_t tmax, double *W, void *stream);
 

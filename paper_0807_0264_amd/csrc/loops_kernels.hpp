@@ -188,11 +188,16 @@ __global__ __launch_bounds__(256) void k_zero(double *p, int n) {
 // take: non-unitary time links, tmax too long for a block (wl_plan), too little scratch.
 // Fields in this form are [t][element][s] complex, s = x + Lx (y + Ly z), t < Lt + tmax.
 
-// largest |(U_3 U_3^dag - 1)_ij| accepted: the rounding of the links' type, so that what the gauge
-// neglects stays below what the products of the general path round away
+// Largest |(U_3 U_3^dag - 1)_ij| (real and imaginary parts) accepted.  The gauge takes each time link's
+// unitary part, where the general path multiplies the link as it is: links that all deviate alike by a
+// scale shift W(R, T) by T times this, and nothing averages that away.  So it is no more than the roundings
+// of a link that was unitary: a unitary matrix rounded to FP32 is off by at most 2^-23 (1.0e-7 in thermalised
+// 32^3x64 fields), its gauge transform or its vortex removal rounded once more by at most 2^-22 (1.7e-7);
+// the same fields in FP64 are off by 1.1e-15 and 2.0e-15.  One FP32 smearing step already leaves 4e-7, ten
+// 1.2e-6: smeared FP32 fields take the general path.
 template <typename T> struct WlTol;
-template <> struct WlTol<float> { static constexpr double v = 1e-6; };
-template <> struct WlTol<double> { static constexpr double v = 1e-13; };
+template <> struct WlTol<float> { static constexpr double v = 2.4e-7; };
+template <> struct WlTol<double> { static constexpr double v = 2.5e-15; };
 // R: the slices of S_k that a wave holds in registers; Q: the slices t whose loops it sums (all read
 // from LDS, so that every wave of a block has a share).  With these a wave needs at most 256 registers (two waves per SIMD).
 template <typename T> struct WlTile;

@@ -62,6 +62,32 @@ def path_loops():
             assert err < (1e-13 if prec == 0 else 2e-6), (L, prec, tmax, bad, err)
 
 
+def cold_field(L, prec, steps):
+    """Unit links, the time links scaled by 1 + steps * (unit in the last place of 1): W(R, T) is the
+    scale to the power 2 T, whatever the path multiplies out."""
+    scale = 1 + steps * 2.0 ** (-52 if prec == 0 else -23)
+    U = np.zeros((L[3], L[2], L[1], L[0], 4, 3, 3), np.complex128)
+    U[...] = np.eye(3)
+    U[..., 3, :, :] *= scale
+    return U, scale
+
+
+def path_loops_scaled():
+    """Wilson loops of time links all off by the same few units in the last place: beyond the temporal
+    gauge's tolerance (2.5e-15, FP32 2.4e-7) they come out to the rounding of the 2 T + 2 R products
+    of a loop, within it the gauge may neglect T times the tolerance."""
+    L, tmax = (4, 2, 2, 8), 8
+    for prec, ulp, tol in ((0, 2.0 ** -52, 2.5e-15), (1, 2.0 ** -23, 2.4e-7)):
+        for steps in (1, 2, 3, 5, 6, 40, 200):
+            U, scale = cold_field(L, prec, steps)
+            got = E.wilson_loops(E.links(U, prec), [(1, 0, 0)], 1, tmax)[0, 0]
+            for T in range(1, tmax + 1):
+                err = abs(got[T - 1] / scale ** (2 * T) - 1)
+                gauged = scale ** 2 - 1 <= tol
+                bound = (2 * T + 2) * ulp + (T * tol if gauged else 0.0)
+                assert err <= bound, (prec, steps, T, err, bound)
+
+
 if __name__ == "__main__":
     for name in sys.argv[1:]:
         globals()["path_" + name]()
