@@ -36,7 +36,7 @@ struct mcg_ctx {
   std::string err;
   hipStream_t cap_stream = nullptr;  // stream used only to capture graphs
   DevBuf part, scalars, counts, states, desc, tmpfield, grad_a, grad_b, gC, ckpt, bw_part, w12, g12;
-  DevBuf line_a, line_b, wl_part, wl_res, wl_img;  // Wilson loops: line fields, partial sums, results, images
+  DevBuf wl_lines, wl_res, wl_img;  // Wilson loops: line fields and partial sums, results, images
   std::vector<DevBuf> W, G12, fpart, traj, gring;
   std::vector<DevBuf> smeared;  // mcg_precondition_batch: the smeared fields
   DevBuf pc_part, pc_counts;    // mcg_precondition_batch: margin partials and vortex counters
@@ -910,7 +910,7 @@ mcg_status mcg_destroy(mcg_ctx *ctx) {
   (void)hipDeviceSynchronize();
   DevBuf *bufs[] = {&ctx->part, &ctx->scalars, &ctx->counts, &ctx->states, &ctx->desc, &ctx->tmpfield,
                     &ctx->grad_a, &ctx->grad_b, &ctx->gC, &ctx->ckpt, &ctx->bw_part, &ctx->w12, &ctx->g12,
-                    &ctx->line_a, &ctx->line_b, &ctx->wl_part, &ctx->wl_res, &ctx->wl_img};
+                    &ctx->wl_lines, &ctx->wl_res, &ctx->wl_img};
   for (DevBuf *b : bufs)
     if (b->p) (void)hipFree(b->p);
   for (DevBuf *b : {&ctx->pc_part, &ctx->pc_counts})
@@ -1905,23 +1905,37 @@ std::vector<std::pair<std::vector<int>, int>> path_images(const std::vector<int>
   return out;
 }
 
+// Scratch of the general path: two lines per image and the partial sums, ni images per launch (up to
+// LOOP_IMAGES_PER_LAUNCH, as many as keep their lines within 4 GiB)
+struct LoopScratch {
+  size_t line, part, total;
+  int ni;
+};
+template <typename T> LoopScratch general_scratch(const Geom &g, int tmax) {
+  LoopScratch r;
+  r.line = (size_t)g.V * 9 * 2 * sizeof(T);
+  r.ni = (int)std::max<size_t>(1, std::min<size_t>(LOOP_IMAGES_PER_LAUNCH, ((size_t)4 << 30) / (2 * r.line)));
+  r.part = sizeof(double) * (size_t)r.ni * tmax * line_blocks(g);
+  r.total = 2 * r.line * r.ni + r.part;
+  return r;
+}
+
+// The loops with their time sides multiplied out: any links.
 template <typename T>
 mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t *vec, int rmax, int tmax,
-                       double *W, hipStream_t s) {
-  // the loops with their time sides multiplied out: any links
+                          double *W, hipStream_t s) {
   const Geom g = geom_of(U->d);
-  const size_t line_bytes = (size_t)g.V * 9 * 2 * sizeof(T);
   const int nres = nvec * rmax * tmax;
-  // images per launch: up to LOOP_IMAGES_PER_LAUNCH, as many as keep their line fields within 4 GiB
-  const int ni = (int)std::max<size_t>(
-      1, std::min<size_t>(LOOP_IMAGES_PER_LAUNCH, ((size_t)4 << 30) / (2 * line_bytes)));
+  const LoopScratch sc = general_scratch<T>(g, tmax);
+  const int ni = sc.ni;
   mcg_status st;
-  if ((st = ensure(ctx, ctx->line_a, line_bytes * ni)) || (st = ensure(ctx, ctx->line_b, line_bytes * ni)) ||
-      (st = ensure(ctx, ctx->wl_part, sizeof(double) * (size_t)ni * tmax * line_blocks(g))) ||
+  if ((st = ensure(ctx, ctx->wl_lines, sc.total)) ||
       (st = ensure(ctx, ctx->wl_res, sizeof(double) * (size_t)nres)) ||
       (st = ensure(ctx, ctx->wl_img, sizeof(LoopImage<T>) * ni)) ||
       (st = ensure_pinned(ctx, sizeof(LoopImage<T>) * ni)))
     return st;
+  char *lines = (char *)ctx->wl_lines.p;
+  double *part = (double *)(lines + 2 * sc.line * ni);
   double *res = (double *)ctx->wl_res.p;
   LoopImage<T> *hI = (LoopImage<T> *)ctx->h_pinned;
   const LoopImage<T> *dI = (const LoopImage<T> *)ctx->wl_img.p;
@@ -1946,14 +1960,14 @@ mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, int nvec, const int3
         }
         // Re tr / 3, averaged over sites and images
         d.weight = (double)e.second / (3.0 * (double)nimg * (double)g.V);
-        d.a = (V2<T> *)((char *)ctx->line_a.p + (size_t)j * line_bytes);
-        d.b = (V2<T> *)((char *)ctx->line_b.p + (size_t)j * line_bytes);
+        d.a = (V2<T> *)(lines + (size_t)j * sc.line);
+        d.b = (V2<T> *)(lines + (size_t)(ni + j) * sc.line);
         hI[j] = d;
       }
       HIPCHK(hipMemcpyAsync(ctx->wl_img.p, hI, sizeof(LoopImage<T>) * n, hipMemcpyHostToDevice, s));
       for (int k = 1; k <= rmax; k++) {
         HIPCHK(launch_lines<T>(g, U->ptr, dI, n, k, s));
-        HIPCHK(launch_wloops<T>(g, U->ptr, dI, n, k, tmax, (double *)ctx->wl_part.p,
+        HIPCHK(launch_wloops<T>(g, U->ptr, dI, n, k, tmax, part,
                                 res + (size_t)(i * rmax + k - 1) * tmax, s));
       }
     }
@@ -1963,10 +1977,12 @@ mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, int nvec, const int3
   return MCG_OK;
 }
 
-// The loops in the temporal gauge (loops_kernels.hpp): *done is false, and nothing is written to W,
-// when the extents or the scratch do not allow it or a time link is not unitary; the general path
-// then takes the call.  At most as many images share a launch as keep the scratch within that of the
-// general path.
+// The loops in the temporal gauge (loops_kernels.hpp): *done is false when the extents or the scratch do
+// not allow it or a time link is not unitary; the general path then takes the call.
+// Both paths keep their lines and partial sums in one buffer, and as many images share a launch as
+// keep it within what the general path holds, so a call leaves no more scratch behind than that path
+// and leaves it room.  Lattices so large that one image exceeds this (the gauged links are three
+// lines, and the transform, in FP64, shares the image's space) take the buffer for the call only.
 template <typename T>
 mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t *vec, int rmax, int tmax,
                          double *W, hipStream_t s, bool *done) {
@@ -1974,29 +1990,41 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
   const Geom g = geom_of(U->d);
   const WlPlan plan = wl_plan<T>(g, tmax);
   if (!plan.ok) return MCG_OK;
+  auto up = [](size_t n) { return (n + 255) / 256 * 256; };
   const size_t Vs = (size_t)g.L[0] * g.L[1] * g.L[2];
   const size_t hbytes = Vs * plan.TE * 9 * sizeof(double2), abytes = Vs * plan.TE * 9 * sizeof(V2<T>);
   const size_t pbytes = sizeof(double) * (size_t)rmax * tmax * plan.nblk;
   const int nres = nvec * rmax * tmax;
-  const size_t budget = (size_t)4 << 30;
-  const int ni = (int)std::max<size_t>(
-      1, std::min<size_t>(LOOP_IMAGES_PER_LAUNCH, (budget - std::min(budget, 3 * abytes)) / (abytes + pbytes)));
+  // the transform is needed before the first line
+  auto lines_of = [&](int n) { return up(std::max(hbytes, abytes * n)); };
+  auto need = [&](int n) { return up(3 * abytes) + lines_of(n) + pbytes * n; };
+  const size_t held = general_scratch<T>(g, tmax).total;
+  int ni = LOOP_IMAGES_PER_LAUNCH;
+  while (ni > 1 && need(ni) > held) ni--;
+  const bool lend = need(ni) > std::max(held, ctx->wl_lines.cap);
   {
     const std::string err = ctx->err;
-    // the transform h is needed before the first line and shares its space
-    if (ensure(ctx, ctx->line_a, std::max(hbytes, abytes * ni)) || ensure(ctx, ctx->line_b, 3 * abytes) ||
-        ensure(ctx, ctx->wl_part, pbytes * ni) || ensure(ctx, ctx->wl_res, sizeof(double) * (size_t)nres + 64)) {
+    if (ensure(ctx, ctx->wl_lines, need(ni)) || ensure(ctx, ctx->wl_res, sizeof(double) * (size_t)nres + 64)) {
       ctx->err = err;  // no room: the general path, with its own scratch
-      for (DevBuf *b : {&ctx->line_a, &ctx->line_b, &ctx->wl_part, &ctx->wl_res}) release(ctx, *b);
+      release(ctx, ctx->wl_lines);
       return MCG_OK;
     }
   }
+  struct Return {
+    mcg_ctx *ctx;
+    bool lend;
+    ~Return() {
+      if (lend) release(ctx, ctx->wl_lines);
+    }
+  } give_back{ctx, lend};
+  char *links = (char *)ctx->wl_lines.p, *lines = links + up(3 * abytes);
+  double *part = (double *)(lines + lines_of(ni));
   mcg_status st;
   if ((st = ensure_pinned(ctx, 64))) return st;
   int *flag = (int *)ctx->wl_res.p;             // in front of the results, cleared with them
   double *res = (double *)ctx->wl_res.p + 8;
   HIPCHK(launch_zero((double *)ctx->wl_res.p, nres + 8, s));
-  HIPCHK(launch_wl_links<T>(g, U->ptr, ctx->line_a.p, ctx->line_b.p, plan.TE, flag, s));
+  HIPCHK(launch_wl_links<T>(g, U->ptr, lines, links, plan.TE, flag, s));
   for (int i = 0; i < nvec; i++) {
     const int v[3] = {vec[3 * i], vec[3 * i + 1], vec[3 * i + 2]};
     const auto imgs = path_images(staircase_steps(v));
@@ -2017,8 +2045,8 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
         // Re tr / 3, averaged over sites and images
         d.weight = (double)e.second / (3.0 * (double)nimg * (double)g.V);
       }
-      HIPCHK(launch_wl_loops<T>(g, ctx->line_b.p, set, plan, rmax, tmax, ctx->line_a.p,
-                                (double *)ctx->wl_part.p, res + (size_t)i * rmax * tmax, flag, s));
+      HIPCHK(launch_wl_loops<T>(g, links, set, plan, rmax, tmax, lines, part,
+                                res + (size_t)i * rmax * tmax, flag, s));
     }
   }
   int *hflag = (int *)ctx->h_pinned;

@@ -1,6 +1,7 @@
 """More runs of the library built against the emulated HIP runtime (AddressSanitizer + UBSan), one
 function per path; started by tests/test_emu_paths.py in a subprocess with libasan preloaded.  Test
 infrastructure only."""
+import ctypes as C
 import os
 import sys
 
@@ -12,6 +13,7 @@ sys.path[:0] = [ROOT, os.path.dirname(HERE), HERE]
 
 import emu_api as E  # noqa: E402
 from oracle import oracle as O  # noqa: E402
+from paper_0807_0264_amd import _abi as A  # noqa: E402
 from paper_0807_0264_amd import synth as S  # noqa: E402
 
 
@@ -86,6 +88,39 @@ def path_loops_scaled():
                 gauged = scale ** 2 - 1 <= tol
                 bound = (2 * T + 2) * ulp + (T * tol if gauged else 0.0)
                 assert err <= bound, (prec, steps, T, err, bound)
+
+
+def path_loops_scratch():
+    """Wilson loops under a scratch limit that admits either path alone but not their buffers added up:
+    a call refused by the temporal gauge after it was set up (a non-unitary time link), a call that its
+    plan refuses after one that it took, and what a gauged call leaves for other calls."""
+    limit = 6
+    L, tmax = (4, 4, 4, 32), 32  # a line is 147 kB: the general path holds 4.8 MB
+
+    def context():
+        h = C.c_void_p()
+        assert E.lib().mcg_create(C.byref(h), 0) == 0
+        assert E.lib().mcg_set_option(h, A.MCG_OPT_SCRATCH_LIMIT_MIB, limit) == 0
+        E._ctx = h
+
+    def loops(U, tmax):
+        got = E.wilson_loops(E.links(U, 1), [(1, 0, 0)], 1, tmax)
+        assert np.abs(got - O.wilson_loops(U, [(1, 0, 0)], 1, tmax)).max() < 2e-6
+
+    saved = E.ctx()
+    U, bad = loop_field(L, 2210, 1), loop_field(L, 2210, 1, 1.001)
+    context()
+    loops(rounded(bad, 1), tmax)
+    E.check(E.lib().mcg_destroy(E.ctx()))
+    context()
+    loops(U, tmax)
+    E.smear(E.links(field(L, 2211, 1), 0), 0.1, 1.0, 2)  # its temporary is a field of 1.2 MB
+    E.check(E.lib().mcg_destroy(E.ctx()))
+    context()
+    loops(U, tmax)
+    loops(loop_field((4, 4, 2, 64), 2212, 1), 62)
+    E.check(E.lib().mcg_destroy(E.ctx()))
+    E._ctx = saved
 
 
 if __name__ == "__main__":
