@@ -131,15 +131,18 @@ struct WlPlan {
   int TE, own, nseg, nw, nblk;
 };
 template <typename T> WlPlan wl_plan(const Geom &g, int tmax);
-// the spatial links in the gauge into N (3 * TE * 9 * Vs complex of T), by way of H (TE * 9 * Vs complex
-// double); *flag is set where a time link is not unitary
+// the transform to the gauge into H (TE * 9 * Vs complex double); *bad (host memory) is set where a time
+// link is not unitary
 template <typename T>
-hipError_t launch_wl_links(const Geom &g, const void *U, void *H, void *N, int TE, int *flag, hipStream_t s);
+hipError_t launch_wl_gauge(const Geom &g, const void *U, void *H, int TE, int *bad, hipStream_t s);
+// the spatial links in the gauge into N (3 * TE * 9 * Vs complex of T)
+template <typename T>
+hipError_t launch_wl_links(const Geom &g, const void *U, const void *H, void *N, int TE, hipStream_t s);
 // every image's line, and all (k, T) loop sums of the launch added into res[(k - 1) tmax + T - 1];
 // A holds imgs.n * TE * 9 * Vs complex of T, part imgs.n * rmax * tmax * plan.nblk doubles
 template <typename T>
 hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs, const WlPlan &plan,
-                           int rmax, int tmax, void *A, double *part, double *res, const int *flag, hipStream_t s);
+                           int rmax, int tmax, void *A, double *part, double *res, hipStream_t s);
 template <typename T>
 hipError_t launch_vortex_field(const Geom &g, const void *U, const double *G, const int8_t *Z, int mode, void *out,
                                hipStream_t s);

@@ -59,21 +59,26 @@ template <typename T> WlPlan wl_plan(const Geom &g, int tmax) {
 }
 
 template <typename T>
-hipError_t launch_wl_links(const Geom &g, const void *U, void *H, void *N, int TE, int *flag, hipStream_t s) {
+hipError_t launch_wl_gauge(const Geom &g, const void *U, void *H, int TE, int *bad, hipStream_t s) {
   const int Vs = g.L[0] * g.L[1] * g.L[2];
-  k_wl_gauge<T><<<(Vs + 63) / 64, 64 * WL_WAVES, 0, s>>>(g, (const V2<T> *)U, (double2 *)H, TE, flag);
-  k_wl_links<T><<<TE * ((Vs + 255) / 256), 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)H, TE, (V2<T> *)N, flag);
+  k_wl_gauge<T><<<(Vs + 63) / 64, 64 * WL_WAVES, 0, s>>>(g, (const V2<T> *)U, (double2 *)H, TE, bad);
+  return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_wl_links(const Geom &g, const void *U, const void *H, void *N, int TE, hipStream_t s) {
+  const int Vs = g.L[0] * g.L[1] * g.L[2];
+  k_wl_links<T><<<TE * ((Vs + 255) / 256), 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)H, TE, (V2<T> *)N);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs, const WlPlan &plan,
-                           int rmax, int tmax, void *A, double *part, double *res, const int *flag, hipStream_t s) {
+                           int rmax, int tmax, void *A, double *part, double *res, hipStream_t s) {
   const int Vs = g.L[0] * g.L[1] * g.L[2];
   const dim3 gl(plan.TE * ((Vs + 255) / 256), imgs.n), gc(plan.nblk, imgs.n);
-  k_wl_line<T><<<gl, 256, 0, s>>>(g, (const V2<T> *)N, imgs, plan.TE, (V2<T> *)A, flag);
+  k_wl_line<T><<<gl, 256, 0, s>>>(g, (const V2<T> *)N, imgs, plan.TE, (V2<T> *)A);
 #define MCG_WL(TC, NW) \
-  k_wl_corr<T, TC, NW><<<gc, 64 * plan.nw, 0, s>>>(g, (const V2<T> *)A, imgs, plan.TE, plan.own, rmax, tmax, part, flag)
+  k_wl_corr<T, TC, NW><<<gc, 64 * plan.nw, 0, s>>>(g, (const V2<T> *)A, imgs, plan.TE, plan.own, rmax, tmax, part)
   // extents at once: the smallest set that holds tmax, else rounds of 16
   const bool four = wl_waves<T>(tmax) == 4;
   if (tmax <= 4) {
@@ -88,7 +93,7 @@ hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs,
     if (four) MCG_WL(16, 4); else MCG_WL(16, 8);
   }
 #undef MCG_WL
-  k_wl_final<<<rmax * tmax, 256, 0, s>>>(part, plan.nblk, imgs, rmax * tmax, res, flag);
+  k_wl_final<<<rmax * tmax, 256, 0, s>>>(part, plan.nblk, imgs, rmax * tmax, res);
   return hipGetLastError();
 }
 
@@ -99,9 +104,10 @@ hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs,
   template hipError_t launch_wloops<T>(const Geom &, const void *, const LoopImage<T> *, int, int, int, double *, \
                                        double *, hipStream_t);                                             \
   template WlPlan wl_plan<T>(const Geom &, int);                                                           \
-  template hipError_t launch_wl_links<T>(const Geom &, const void *, void *, void *, int, int *, hipStream_t); \
+  template hipError_t launch_wl_gauge<T>(const Geom &, const void *, void *, int, int *, hipStream_t);     \
+  template hipError_t launch_wl_links<T>(const Geom &, const void *, const void *, void *, int, hipStream_t); \
   template hipError_t launch_wl_loops<T>(const Geom &, const void *, const LoopImages &, const WlPlan &, int, int, \
-                                         void *, double *, double *, const int *, hipStream_t);
+                                         void *, double *, double *, hipStream_t);
 MCG_LOOPS_INST(float)
 MCG_LOOPS_INST(double)
 

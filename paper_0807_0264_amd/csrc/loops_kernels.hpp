@@ -245,7 +245,7 @@ __device__ __forceinline__ int wl_index(const Geom &g, const int c[4]) { return 
 // pieces before it from LDS and goes through its piece again (50 slices: 59 us as one chain).
 template <typename T>
 __global__ __launch_bounds__(64 * WL_WAVES) void k_wl_gauge(Geom g, const V2<T> *__restrict__ U,
-                                                           double2 *__restrict__ H, int TE, int *flag) {
+                                                           double2 *__restrict__ H, int TE, int *bad_out) {
   __shared__ double2 piece[WL_WAVES - 1][9][64];
   const int Vs = g.L[0] * g.L[1] * g.L[2];
   const int lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6);
@@ -294,16 +294,14 @@ __global__ __launch_bounds__(64 * WL_WAVES) void k_wl_gauge(Geom g, const V2<T> 
     if (live) wl_store(H, te, Vs, (unsigned)s * 16u, h);
     h = mul(h, unitary(u));
   }
-  if (bad) atomicOr(flag, 1);
+  if (bad) *bad_out = 1;  // the same value from every lane
 }
 
 // The spatial links in the gauge, h(x, t) U_j(x, t) h(x+j, t)^dag for t < TE (links at t modulo Lt),
 // formed in FP64 and rounded once: N + j TE 9 Vs.  One block per (256 spatial sites, t).
 template <typename T>
 __global__ __launch_bounds__(256) void k_wl_links(Geom g, const V2<T> *__restrict__ U,
-                                                  const double2 *__restrict__ H, int TE, V2<T> *__restrict__ N,
-                                                  const int *__restrict__ flag) {
-  if (*flag) return;
+                                                  const double2 *__restrict__ H, int TE, V2<T> *__restrict__ N) {
   const int Vs = g.L[0] * g.L[1] * g.L[2], nsb = (Vs + 255) / 256;
   const int te = (int)blockIdx.x / nsb, s = ((int)blockIdx.x - te * nsb) * 256 + (int)threadIdx.x;
   if (s >= Vs) return;
@@ -327,8 +325,7 @@ __global__ __launch_bounds__(256) void k_wl_links(Geom g, const V2<T> *__restric
 // (15 GB in 1.7 ms at 20^3x40).
 template <typename T>
 __global__ __launch_bounds__(256) void k_wl_line(Geom g, const V2<T> *__restrict__ N, LoopImages imgs, int TE,
-                                                 V2<T> *__restrict__ A, const int *__restrict__ flag) {
-  if (*flag) return;
+                                                 V2<T> *__restrict__ A) {
   const LoopPath &im = imgs.img[blockIdx.y];
   const int Vs = g.L[0] * g.L[1] * g.L[2], nsb = (Vs + 255) / 256;
   const int blk = xcd_range((int)blockIdx.x, (int)gridDim.x);
@@ -408,12 +405,11 @@ template <typename T, typename S> __device__ __forceinline__ void opaque_after(T
 template <typename T, int TC, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void k_wl_corr(Geom g, const V2<T> *__restrict__ A, LoopImages imgs,
                                                           int TE, int own, int rmax, int tmax,
-                                                          double *__restrict__ part, const int *__restrict__ flag) {
+                                                          double *__restrict__ part) {
   constexpr int R = WlTile<T>::R, Q = WlTile<T>::Q;
   constexpr int ROWS = NW * R + Q + TC;  // read past the slices held, for extents above tmax or with x = 0
   constexpr int TP = TC > 8 ? 16 : TC;
   __shared__ V2<T> ex[2][ROWS * 64];
-  if (*flag) return;
   const LoopPath &im = imgs.img[blockIdx.y];
   const int Vs = g.L[0] * g.L[1] * g.L[2], nsc = (Vs + 63) / 64;
   const int lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6), nw = blockDim.x >> 6;
@@ -499,8 +495,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_wl_corr(Geom g, const V2<T> *__r
 // res[i] += sum over the images of weight * sum over the blocks of part, i = (k - 1) tmax + T - 1: one
 // block per i, terms in a fixed order
 __global__ __launch_bounds__(256) void k_wl_final(const double *__restrict__ part, int nb, LoopImages imgs, int nres,
-                                                  double *res, const int *__restrict__ flag) {
-  if (*flag) return;
+                                                  double *res) {
   double v = 0.0;
   for (int i = 0; i < imgs.n; i++) {
     const double *p = part + ((size_t)i * nres + blockIdx.x) * nb;

@@ -1977,8 +1977,11 @@ mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, int nvec, const int3
   return MCG_OK;
 }
 
-// The loops in the temporal gauge (loops_kernels.hpp): *done is false when the extents or the scratch do
-// not allow it or a time link is not unitary; the general path then takes the call.
+// The loops in the temporal gauge (loops_kernels.hpp): *done is false, and nothing is written to W, when
+// the extents or the scratch do not allow it or a time link is not unitary; the general path then takes
+// the call.  The host reads whether they are as soon as the transform is formed, before it launches the
+// loops: a synchronisation of 10 us, where a call that is refused cost three launches per chunk of
+// images and two copies.
 // Both paths keep their lines and partial sums in one buffer, and as many images share a launch as
 // keep it within what the general path holds, so a call leaves no more scratch behind than that path
 // and leaves it room.  Lattices so large that one image exceeds this (the gauged links are three
@@ -2004,7 +2007,7 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
   const bool lend = need(ni) > std::max(held, ctx->wl_lines.cap);
   {
     const std::string err = ctx->err;
-    if (ensure(ctx, ctx->wl_lines, need(ni)) || ensure(ctx, ctx->wl_res, sizeof(double) * (size_t)nres + 64)) {
+    if (ensure(ctx, ctx->wl_lines, need(ni)) || ensure(ctx, ctx->wl_res, sizeof(double) * (size_t)nres)) {
       ctx->err = err;  // no room: the general path, with its own scratch
       release(ctx, ctx->wl_lines);
       return MCG_OK;
@@ -2020,11 +2023,15 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
   char *links = (char *)ctx->wl_lines.p, *lines = links + up(3 * abytes);
   double *part = (double *)(lines + lines_of(ni));
   mcg_status st;
-  if ((st = ensure_pinned(ctx, 64))) return st;
-  int *flag = (int *)ctx->wl_res.p;             // in front of the results, cleared with them
-  double *res = (double *)ctx->wl_res.p + 8;
-  HIPCHK(launch_zero((double *)ctx->wl_res.p, nres + 8, s));
-  HIPCHK(launch_wl_links<T>(g, U->ptr, lines, links, plan.TE, flag, s));
+  if ((st = ensure_results(ctx))) return st;
+  int *bad = (int *)ctx->h_res;
+  *bad = 0;
+  HIPCHK(launch_wl_gauge<T>(g, U->ptr, lines, plan.TE, bad, s));
+  HIPCHK(hipStreamSynchronize(s));
+  if (*bad) return MCG_OK;
+  double *res = (double *)ctx->wl_res.p;
+  HIPCHK(launch_zero(res, nres, s));
+  HIPCHK(launch_wl_links<T>(g, U->ptr, lines, links, plan.TE, s));
   for (int i = 0; i < nvec; i++) {
     const int v[3] = {vec[3 * i], vec[3 * i + 1], vec[3 * i + 2]};
     const auto imgs = path_images(staircase_steps(v));
@@ -2046,14 +2053,12 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
         d.weight = (double)e.second / (3.0 * (double)nimg * (double)g.V);
       }
       HIPCHK(launch_wl_loops<T>(g, links, set, plan, rmax, tmax, lines, part,
-                                res + (size_t)i * rmax * tmax, flag, s));
+                                res + (size_t)i * rmax * tmax, s));
     }
   }
-  int *hflag = (int *)ctx->h_pinned;
-  HIPCHK(hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync(W, res, sizeof(double) * nres, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  *done = *hflag == 0;
+  *done = true;
   return MCG_OK;
 }
 

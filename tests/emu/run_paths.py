@@ -123,6 +123,27 @@ def path_loops_scratch():
     E._ctx = saved
 
 
+def path_loops_refused():
+    """A field with a non-unitary time link, under a scratch limit that admits the temporal gauge and not
+    the general path: the call is refused and W is not touched."""
+    L, tmax = (4, 4, 4, 32), 8
+    saved = E.ctx()
+    h = C.c_void_p()
+    assert E.lib().mcg_create(C.byref(h), 0) == 0
+    assert E.lib().mcg_set_option(h, A.MCG_OPT_SCRATCH_LIMIT_MIB, 4) == 0
+    E._ctx = h
+    for bad, status in ((None, A.MCG_OK), (1.001, A.MCG_ENOMEM)):
+        U = E.links(rounded(loop_field(L, 2220, 1, bad), 1), 1)
+        f = U.abi()
+        W = np.full((1, 1, tmax), 7.0)
+        st = E.lib().mcg_wilson_loops(h, C.byref(f), 1, (C.c_int32 * 3)(1, 0, 0), 1, tmax,
+                                      W.ctypes.data_as(C.POINTER(C.c_double)), None)
+        assert st == status, (st, E.lib().mcg_last_error(h))
+        assert (W == 7.0).all() == (bad is not None), W
+    E.check(E.lib().mcg_destroy(h))
+    E._ctx = saved
+
+
 if __name__ == "__main__":
     for name in sys.argv[1:]:
         globals()["path_" + name]()
