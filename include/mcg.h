@@ -248,8 +248,9 @@ mcg_status mcg_precondition_batch(mcg_ctx *ctx, int32_t B, const mcg_field *U, d
  * partial sums: results at one variant are deterministic.  Launches too small
  * to fill the device (up to 65,536 sites over a batch with FP32 links, 32,768
  * with FP64) use another form of the kernel, one wave per link, with the same
- * results, unless mcg_set_variant has been called for that precision and form;
- * mcg_tune_batch times that form as the schedule in use. */
+ * results, until a variant is tuned or set for that precision and form, which
+ * then is what every fix runs; mcg_tune_batch, before that, times that form as
+ * the schedule in use. */
 #define MCG_NUM_VARIANTS 6
 mcg_status mcg_autotune(mcg_ctx *ctx, const mcg_field *U, int32_t *best_variant,
                         double *ms_per_halfsweep, void *stream);

@@ -57,8 +57,7 @@ struct mcg_ctx {
   size_t scratch_used = 0;
   int stop_every = 1;  // stop test only after sweeps numbered by multiples of this (MCG_OPT_STOP_EVERY)
   int variant[2][2] = {{2, 2}, {2, 2}};  // half-sweep variant per [precision][two-row form]
-  enum { DEFAULT, TUNED, SET };
-  int variant_from[2][2] = {};  // who chose it: nobody, mcg_autotune or the caller (mcg_set_variant)
+  bool variant_chosen[2][2] = {};  // by mcg_autotune or mcg_set_variant: then it is what runs
   // launch variant and schedule chosen by mcg_tune_batch, per batch shape (tune_key); used by the
   // fixes of that shape until an explicit variant or schedule option is set
   std::map<std::string, std::pair<mcg_tune_choice, bool>> tuned;  // the bool: one wave per link
@@ -332,8 +331,8 @@ static int tile_order(int order, int par) { return order == 0 ? 0 : (order == 2 
 // this batch shape (precision, storage form, transform ring, update variant, the fields' extents in
 // order), else the context's variant and options.  Re-linearisation hits and exact steps run with
 // 256-thread blocks (variant 2).  Every choice gives the same bits.
-// Where the caller set no variant (mcg_set_variant), a launch of few sites runs one wave per link
-// (k_halfsweep_wide) instead, and mcg_tune_batch times that form as the schedule in use.
+// Where no variant was tuned (mcg_autotune) or set (mcg_set_variant), a launch of few sites runs one
+// wave per link (k_halfsweep_wide) instead, and mcg_tune_batch times that form as the schedule in use.
 struct Sched {
   int variant, order, paired, nslab;
   bool wide = false;
@@ -344,7 +343,7 @@ struct Sched {
 // 32.7 against 26.2-28.5 at 512, where a second round of blocks has begun.
 constexpr int WIDE_BLOCKS_F32 = 512, WIDE_BLOCKS_F64 = 256;
 bool wide_launch(const mcg_ctx *ctx, int B, const mcg_field *U) {
-  if (!ctx->c12 || ctx->hits > 1 || ctx->exact || ctx->variant_from[U[0].prec][1] == mcg_ctx::SET) return false;
+  if (!ctx->c12 || ctx->hits > 1 || ctx->exact || ctx->variant_chosen[U[0].prec][1]) return false;
   int64_t n = 0;
   for (int b = 0; b < B; b++) n += nblocks(geom_of(U[b].d), 64);
   return n <= (U[0].prec == MCG_F32 ? WIDE_BLOCKS_F32 : WIDE_BLOCKS_F64);
@@ -366,7 +365,7 @@ std::string tune_key(const mcg_ctx *ctx, int B, const mcg_field *U) {
 // 3.39 against 3.42).
 int variant_of(const mcg_ctx *ctx, int B, const mcg_field *U, bool c12) {
   const int prec = U[0].prec;
-  if (c12 && ctx->variant_from[prec][1] == mcg_ctx::DEFAULT) {
+  if (c12 && !ctx->variant_chosen[prec][1]) {
     int64_t V = 0;
     for (int b = 0; b < B; b++) V += geom_of(U[b].d).V;
     if (prec == MCG_F64 && (V < 120000 || V >= 600000)) return 0;
@@ -1339,7 +1338,7 @@ static mcg_status autotune_impl(mcg_ctx *ctx, int B, const mcg_field *U, int32_t
   (void)hipEventDestroy(e1);
   if (rc) return rc;
   ctx->variant[prec][c12] = vbest;
-  ctx->variant_from[prec][c12] = mcg_ctx::TUNED;
+  ctx->variant_chosen[prec][c12] = true;
   if (best) *best = vbest;
   return MCG_OK;
 }
@@ -1556,7 +1555,7 @@ mcg_status mcg_set_variant(mcg_ctx *ctx, int32_t prec, int32_t variant) {
   if ((prec != MCG_F64 && prec != MCG_F32) || variant < 0 || variant >= NUM_VARIANTS)
     return fail(ctx, MCG_EINVAL, "bad precision or variant");
   ctx->variant[prec][ctx->c12] = variant;
-  ctx->variant_from[prec][ctx->c12] = mcg_ctx::SET;
+  ctx->variant_chosen[prec][ctx->c12] = true;
   return MCG_OK;
 }
 

@@ -202,10 +202,21 @@ template <typename F> void run_grid(dim3 grid, dim3 block, F body) {
         LanePool::get().run(nthreads, lane);
       }
 }
+// names of the kernels launched so far, as written in the launchers
+inline std::vector<const char *> launched;
+
 }  // namespace emu
+
+// how many launches so far were of a kernel whose name contains `part`
+extern "C" inline __attribute__((used)) int emu_launches(const char *part) {
+  int n = 0;
+  for (const char *k : emu::launched) n += std::strstr(k, part) != nullptr;
+  return n;
+}
 
 // kernel launch: EMU_LAUNCH(kernel, grid, block, stream, args...)
 #define EMU_LAUNCH(KERNEL, GRID, BLOCK, STREAM, ...)                              \
+  emu::launched.push_back(#KERNEL),                                               \
   emu::submit((STREAM), [=] { emu::run_grid(dim3(GRID), dim3(BLOCK), [=] { KERNEL(__VA_ARGS__); }); })
 
 inline hipError_t hipGetLastError() { return hipSuccess; }

@@ -144,6 +144,27 @@ def path_loops_refused():
     E._ctx = saved
 
 
+def path_launch_form():
+    """The form of the half-sweep that a small fix launches: one wave per link until a variant was chosen,
+    by the autotuner or by the caller, which then is what runs."""
+    saved = E.ctx()
+    launches = E.lib().emu_launches
+    for prec in (0, 1):
+        U = E.links(field((4, 4, 4, 4), 2230, 1), prec)
+        for choose in (None, lambda: E.autotune_batch([U]), lambda: E.set_variant(prec, 1)):
+            h = C.c_void_p()
+            assert E.lib().mcg_create(C.byref(h), 0) == 0
+            E._ctx = h
+            if choose:
+                choose()
+            before = launches(b"k_halfsweep_wide"), launches(b"k_halfsweep<")
+            E.fix(U, None, tol=-1.0, max_sweeps=2)
+            wide, plain = (launches(k) - n for k, n in zip((b"k_halfsweep_wide", b"k_halfsweep<"), before))
+            assert (wide, plain) == ((4, 0) if choose is None else (0, 4)), (prec, wide, plain)
+            E.check(E.lib().mcg_destroy(h))
+    E._ctx = saved
+
+
 if __name__ == "__main__":
     for name in sys.argv[1:]:
         globals()["path_" + name]()
