@@ -775,12 +775,13 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
   const size_t fb = field_bytes(U->d, U->prec);
   const int c = (ckpt_every <= 0 || ckpt_every > n) ? std::max(n, 1) : ckpt_every;
   const int nck = n > 0 ? (n + c - 1) / c : 0;
-  // fields: nck checkpoints, c-1 segment slots, 2 forward temporaries, 2 gradients, grad_C, the
-  // staple sums (Cp, and Cr for eps != 1) of the first c-1 steps of a segment, and those of every
-  // segment's last step, which the forward pass stores.  If that does not fit, the sums are not
-  // kept and the adjoint's first pass forms the staples itself (the same results, more time).
-  const int ncs = eps == 1.0 ? 1 : 2;
-  const size_t nbase = (size_t)nck + (size_t)(c - 1) + 5;
+  // fields: nkept checkpoints (U itself is the first segment's), c-1 segment slots, 2 forward
+  // temporaries, 2 gradients, grad_C, the staple sums (Cp, and Cr for eps != 1) of the first c-1 steps of
+  // a segment, and those of every segment's last step, which the forward pass stores.  If that does not
+  // fit, the sums are not kept and the adjoint's first pass forms the staples itself (the same results,
+  // more time).
+  const int ncs = eps == 1.0 ? 1 : 2, nkept = std::max(nck - 1, 0);
+  const size_t nbase = (size_t)nkept + (size_t)(c - 1) + 5;
   const size_t nfields = nbase + (size_t)(c - 1) * ncs + (size_t)nck * ncs;
   mcg_status st;
   bool stored = true;
@@ -797,13 +798,15 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
   if ((st = ensure(ctx, ctx->bw_part, sizeof(double) * nparts + 64)) || (st = ensure_results(ctx))) return st;
   char *base = (char *)ctx->ckpt.p;
   auto slot = [&](size_t i) { return (void *)(base + i * fb); };
-  void *tmp0 = slot(nck + c - 1), *tmp1 = slot(nck + c), *gA = slot(nck + c + 1), *gB = slot(nck + c + 2),
-       *gC = slot(nck + c + 3);
+  auto ckpt = [&](int seg) { return slot((size_t)seg - 1); };       // the field a segment starts from, seg > 0
+  auto in_seg = [&](int j) { return slot((size_t)nkept + j - 1); };  // ... and after step j of it, 0 < j < c
+  char *work = (char *)slot((size_t)nkept + (c - 1));
+  void *tmp0 = work, *tmp1 = work + fb, *gA = work + 2 * fb, *gB = work + 3 * fb, *gC = work + 4 * fb;
   auto csum = [&](int j) -> void * {  // step j < c-1 of a segment
-    return stored ? slot((size_t)nck + c + 4 + (size_t)j * ncs) : nullptr;
+    return stored ? slot(nbase + (size_t)j * ncs) : nullptr;
   };
   auto clast = [&](int seg) -> void * {  // a segment's last step
-    return stored ? slot((size_t)nck + c + 4 + (size_t)(c - 1) * ncs + (size_t)seg * ncs) : nullptr;
+    return stored ? slot(nbase + (size_t)(c - 1) * ncs + (size_t)seg * ncs) : nullptr;
   };
   double *part = (double *)ctx->bw_part.p;
   int *flag = (int *)(part + nparts);  // the adjoint's range flag
@@ -819,9 +822,9 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
     const Range range_("backward: forward smearing");
     for (int k = 0; k < n; k++) {
       const bool in_last = k >= k0_last && k < n - 1;
-      // a step whose result is a checkpoint writes it there; U itself is the first one
-      void *nxt = (k + 1) % c == 0 && k + 1 < n ? slot((k + 1) / c)
-                  : in_last                     ? slot((size_t)nck + (k - k0_last))
+      // a step whose result is a checkpoint writes it there
+      void *nxt = (k + 1) % c == 0 && k + 1 < n ? ckpt((k + 1) / c)
+                  : in_last                     ? in_seg(k + 1 - k0_last)
                                                 : (cur == tmp0 ? tmp1 : tmp0);
       const bool last = k % c == c - 1 || k == n - 1;
       void *cs = last ? clast(k / c) : in_last ? csum(k - k0_last) : nullptr;
@@ -838,9 +841,9 @@ mcg_status backward_impl(mcg_ctx *ctx, const mcg_field *U, double rho, double ep
     // step forms (the last step's were kept by the forward pass), which the first pass of the
     // adjoint reads
     std::vector<const void *> fields(len);
-    fields[0] = seg == 0 ? U->ptr : slot(seg);
+    fields[0] = seg == 0 ? U->ptr : ckpt(seg);
     for (int j = 1; j < len; j++) {
-      void *dst = slot(nck + j - 1);
+      void *dst = in_seg(j);
       if (seg < nck - 1) HIPCHK(launch_smear_step<T>(g, fields[j - 1], dst, rho, eps, s, csum(j - 1)));
       fields[j] = dst;
     }

@@ -165,6 +165,23 @@ def path_launch_form():
     E._ctx = saved
 
 
+def path_backward_workspace():
+    """The gradient's smallest workspace, as mcg.h states it: ceil(n/c) - 1 + (c - 1) + 5 fields."""
+    L, n, c = (4, 4, 4, 16), 3, 1  # 7 fields of 590 kB
+    U, G = E.links(field(L, 2240, 1), 0), E.gauge(S.haar_gauge(L, S.sub_seed(2241)))
+    want = E.smear_mcg_backward(U, 0.1, 1.0, n, G, c)
+    saved = E.ctx()
+    h = C.c_void_p()
+    assert E.lib().mcg_create(C.byref(h), 0) == 0
+    assert E.lib().mcg_set_option(h, A.MCG_OPT_SCRATCH_LIMIT_MIB, 4) == 0
+    E._ctx = h
+    got = E.smear_mcg_backward(U, 0.1, 1.0, n, G, c)
+    assert np.abs(E.host_links(got[0]) - E.host_links(want[0])).max() <= 1e-13 * np.abs(E.host_links(want[0])).max()
+    assert all(abs(a - b) <= 1e-12 * abs(b) for a, b in zip(got[1:], want[1:])), (got[1:], want[1:])
+    E.check(E.lib().mcg_destroy(h))
+    E._ctx = saved
+
+
 if __name__ == "__main__":
     for name in sys.argv[1:]:
         globals()["path_" + name]()
