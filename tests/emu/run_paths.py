@@ -64,6 +64,19 @@ def path_loops():
             assert err < (1e-13 if prec == 0 else 2e-6), (L, prec, tmax, bad, err)
 
 
+def path_loops_extents():
+    """Wilson loops at the edges of every set of extents that the correlations are built for."""
+    L = (2, 2, 2, 18)
+    for prec in (0, 1):
+        U = loop_field(L, 2250, prec)
+        want = O.wilson_loops(U, [(1, 0, 0)], 2, 18)
+        for tmax in (1, 4, 5, 8, 9, 10, 11, 12, 13, 16, 17, 18):
+            before = E.lib().emu_launches(b"k_wl_corr")
+            got = E.wilson_loops(E.links(U, prec), [(1, 0, 0)], 2, tmax)
+            assert E.lib().emu_launches(b"k_wl_corr") == before + 1, (prec, tmax)
+            assert np.abs(got - want[..., :tmax]).max() < (1e-13 if prec == 0 else 2e-6), (prec, tmax)
+
+
 def cold_field(L, prec, steps):
     """Unit links, the time links scaled by 1 + steps * (unit in the last place of 1): W(R, T) is the
     scale to the power 2 T, whatever the path multiplies out."""
