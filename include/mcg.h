@@ -294,9 +294,9 @@ mcg_status mcg_tune_batch(mcg_ctx *ctx, int32_t B, const mcg_field *U, mcg_tune_
                           void *stream);
 mcg_status mcg_clear_tuning(mcg_ctx *ctx);
 mcg_status mcg_set_variant(mcg_ctx *ctx, int32_t prec, int32_t variant);
-/* The variant last set or tuned for prec and the context's form, 2 at first
- * (until then, in the two-row form, fixes of 600,000 sites or more run variant
- * 1 with FP32 links and 0 with FP64, those of up to 120,000 with FP64 0). */
+/* The variant last set or tuned for prec and the context's form; at first 0 for
+ * FP64 in the two-row form and 2 otherwise (until then FP32 fixes of 600,000
+ * sites or more in the two-row form run variant 1). */
 mcg_status mcg_get_variant(mcg_ctx *ctx, int32_t prec, int32_t *variant);
 
 /* ---- options ----------------------------------------------------------------------- */

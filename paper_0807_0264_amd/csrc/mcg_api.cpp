@@ -56,7 +56,10 @@ struct mcg_ctx {
   size_t scratch_limit = 0;  // bytes of device scratch the context may hold, 0 = no limit
   size_t scratch_used = 0;
   int stop_every = 1;  // stop test only after sweeps numbered by multiples of this (MCG_OPT_STOP_EVERY)
-  int variant[2][2] = {{2, 2}, {2, 2}};  // half-sweep variant per [precision][two-row form]
+  // half-sweep variant per [precision][two-row form].  FP64 in two rows: 64-thread blocks; us per sweep of
+  // a fix against 256-thread ones: 12^3x24 29.6 (31.3), 16^3x24 41.5 (42.1), 16^3x32 48.7 (48.4), 24x16^2x32
+  // 72.7 (72.4), 20^3x40 113.1 (113.4), 24^3x32 147.6 (151.4), 24^3x48 232 (239), 32^3x64 768 (811)
+  int variant[2][2] = {{2, 0}, {2, 2}};
   bool variant_chosen[2][2] = {};  // by mcg_autotune or mcg_set_variant: then it is what runs
   // launch variant and schedule chosen by mcg_tune_batch, per batch shape (tune_key); used by the
   // fixes of that shape until an explicit variant or schedule option is set
@@ -357,19 +360,17 @@ std::string tune_key(const mcg_ctx *ctx, int B, const mcg_field *U) {
   }
   return k;
 }
-// The variant where nobody chose one, two-row form.  FP64: 64-thread blocks (60 sweeps of 14^4 1.80 against
-// 1.91 ms with 256 threads, 16^3x20 2.16 against 2.22; 50 of 32^3x64 36.0 against 37.9), except between
-// 120,000 and 600,000 sites (16^3x32 2.95 against 2.91 ms per 60, 20^3x40 the same).  FP32: 128 from
-// 600,000 sites in the launch on (the benchmark's four lattices 70.5 against 70.8-71.6 ms per 150 sweeps,
-// 16 copies of 16^4 16.0 against 16.3), 256 below (16^3x20 1.64 against 1.78 ms per 60 with 128, 20^3x40
-// 3.39 against 3.42).
+// The variant where nobody chose one.  FP32 in two rows: 128-thread blocks from 600,000 sites in the
+// launch on, 256-thread ones below; us per sweep of a fix with 128 (256): 98,304 sites 29.8 (27.7), 131,072
+// 31.7 (30.6), 160,000 34.3 (35.5), 196,608 37.5 (37.4), 320,000 56.4 (56.1), 442,368 70.7 (70.4), 8 copies of
+// 16^4 81.5 (80.3); 663,552 100.8 (102.1), 702,464 115.4 (116.8), 884,736 140.5 (140.9), 32^4 165.8 (164.7),
+// 16 copies of 16^4 177.5 (178.1), 32^3x64 345 (350).
 int variant_of(const mcg_ctx *ctx, int B, const mcg_field *U, bool c12) {
   const int prec = U[0].prec;
-  if (c12 && !ctx->variant_chosen[prec][1]) {
+  if (prec == MCG_F32 && c12 && !ctx->variant_chosen[prec][1]) {
     int64_t V = 0;
     for (int b = 0; b < B; b++) V += geom_of(U[b].d).V;
-    if (prec == MCG_F64 && (V < 120000 || V >= 600000)) return 0;
-    if (prec == MCG_F32 && V >= 600000) return 1;
+    if (V >= 600000) return 1;
   }
   return ctx->variant[prec][c12];
 }

@@ -170,6 +170,11 @@ def path_launch_form():
             E._ctx = h
             if choose:
                 choose()
+            else:  # the two-row form, then the full one
+                assert E.get_variant(prec) == (0 if prec == 0 else 2)
+                E.set_two_row(False)
+                assert E.get_variant(prec) == 2
+                E.set_two_row(True)
             before = launches(b"k_halfsweep_wide"), launches(b"k_halfsweep<")
             E.fix(U, None, tol=-1.0, max_sweeps=2)
             wide, plain = (launches(k) - n for k, n in zip((b"k_halfsweep_wide", b"k_halfsweep<"), before))
