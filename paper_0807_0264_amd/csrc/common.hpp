@@ -311,9 +311,13 @@ __device__ __forceinline__ int xcd_range(int i, int n) {
   return x * q + (x < r ? x : r) + (i >> 3);
 }
 // One block's value handed to another block of the same launch, without a fence (which would write back
-// and invalidate the L2 of every block's XCD): stores and loads of device scope go past the L2s to the
-// memory that all XCDs share, so a store that has been waited for is seen by every later load of
-// device scope.
+// and invalidate the L2 of every block's XCD).  The language's memory model orders nothing here, since all
+// accesses are relaxed; what does is how the compiler forms them for gfx950, the only target: atomic loads
+// and stores of device scope carry sc1, which sends them past the L2s to the memory that all XCDs share,
+// and s_waitcnt vmcnt(0) returns once such a store has arrived there.  So a value stored, waited for
+// (wait_memory, by the storing thread) and then counted by a device-scope atomic is seen by every
+// device-scope load issued after that count was read.  A release and an acquire would make the same
+// promise for ordinary accesses too, by the write-back and invalidation that this avoids.
 __device__ __forceinline__ void store_device(double *p, double v) {
 #if defined(__HIP_DEVICE_COMPILE__)
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

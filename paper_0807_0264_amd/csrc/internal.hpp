@@ -125,7 +125,7 @@ struct LoopImages {
   LoopPath img[LOOP_IMAGES_PER_LAUNCH];
 };
 // How the temporal-gauge kernels cover (t, T): blocks of nw waves for nseg ranges of `own` slices
-// each (ok = false: tmax is beyond what a block can hold, or the launch would be too wide)
+// each (ok = false: tmax is beyond what a block can hold)
 struct WlPlan {
   bool ok;
   int TE, own, nseg, nw, nblk;

@@ -279,6 +279,7 @@ __device__ __forceinline__ void staples(const Geom &g, const Links<T> &L, int pa
     mac_nd(ahead, L.load_off(mu, x0.odd(m1)), Cr);
     return;
   }
+  // FP32 from here on
   const M3<T> umu_xmm = L.load_off(mu, x0.odd(m_1));  // U_mu(x-mu)
   for (int nu = 0; nu < 4; nu++) {
     if (nu == mu) continue;
