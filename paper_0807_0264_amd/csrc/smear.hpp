@@ -199,9 +199,9 @@ __device__ __forceinline__ void staples(const Geom &g, const Links<T> &L, int pa
   const Around<T> x0(L, par, h);
   const int m1 = move_by<T>(g, c, mu, +1);
   if constexpr (!OI) {
-    // Stout: the six links of a direction are loaded together and (FP32) held until all six are in,
-    // so a wave has six loads in flight instead of three; 142 VGPRs and three waves per SIMD
-    // instead of 94 and five, 1.7 % less time.  The directions are taken as mu ^ 1, mu ^ 2, mu ^ 3, the
+    // Stout, for small launches and for the adjoint where the forward pass's staple sums did not fit:
+    // the six links of a direction are loaded together and (FP32) held until all six are in, so a wave
+    // has six loads in flight instead of three.  The directions are taken as mu ^ 1, mu ^ 2, mu ^ 3, the
     // order of k_smear_stout.
     for (int j = 1; j < 4; j++) {
       const int nu = mu ^ j;

@@ -6,9 +6,10 @@
 
 namespace mcg {
 
-// Over-improved stout, a thread per link.  CS = 1: also store the staple sums Cp and Cr of every link
-// in Cst, as two link fields [Cp | Cr], for the adjoint's first pass
-template <typename T, int CS = 0>
+// A thread per link: over-improved stout (OI), and stout where k_smear_stout's blocks are too coarse
+// (stout_in_blocks).  CS = 1: also store the staple sums Cp (and Cr, OI) of every link in Cst, as two link
+// fields [Cp | Cr], for the adjoint's first pass
+template <typename T, bool OI, int CS = 0>
 __global__ __launch_bounds__(128, sizeof(T) == 4 ? 2 : 1) void k_smear(Geom g, const V2<T> *__restrict__ U,
                                                V2<T> *__restrict__ out, T rho, T wp, T wr,
                                                V2<T> *__restrict__ Cst = nullptr) {
@@ -22,14 +23,17 @@ __global__ __launch_bounds__(128, sizeof(T) == 4 ? 2 : 1) void k_smear(Geom g, c
   const int mu = (w & 7) >> 1, par = w & 1;
   const Links<T> L{const_cast<V2<T> *>(U), g.Vh};
   M3<T> Cp, Cr;
-  staples<T, true>(g, L, par, h, mu, Cp, Cr);
+  staples<T, OI>(g, L, par, h, mu, Cp, Cr);
   if constexpr (CS != 0) {
     Links<T>{Cst, g.Vh}.store(mu, par, h, Cp);
-    Links<T>{Cst + (size_t)72 * g.Vh, g.Vh}.store(mu, par, h, Cr);
+    if (OI) Links<T>{Cst + (size_t)72 * g.Vh, g.Vh}.store(mu, par, h, Cr);
   }
   M3<T> C;
 #pragma unroll
-  for (int k = 0; k < 9; k++) C.e[k] = rho * (wp * Cp.e[k] + wr * Cr.e[k]);
+  for (int k = 0; k < 9; k++) {
+    C.e[k] = rho * (wp * Cp.e[k]);
+    if (OI) C.e[k] = rho * (wp * Cp.e[k] + wr * Cr.e[k]);
+  }
   const M3<T> u = L.load(mu, par, h);
   const M3<T> E = exp_su3(ta(mul_nd(C, u)));
   Links<T>{out, g.Vh}.store(mu, par, h, mul(E, u));
@@ -43,7 +47,7 @@ __global__ __launch_bounds__(128, sizeof(T) == 4 ? 2 : 1) void k_smear(Geom g, c
 // XCD's L2 holds.  CS = 1: also store Cp in Cst; the sums in the order of staples<T, false>.
 // 32^3x64 FP32, per step: 0.802 ms with a wave per link and 19 loads, 0.767 with the exchange at three
 // waves per SIMD, 0.747 at four, 0.713 with the groups of four (of two: 0.744): 76 % of the VALU issue
-// rate.  FP64, 20^3x40 and 16^4: 0.136 -> 0.123 ms on average.
+// rate.  FP64, 20^3x40 and 16^4: 0.136 -> 0.123 ms on average.  Same bits as k_smear<T, false>.
 template <typename T, int CS = 0>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_smear_stout(Geom g, const V2<T> *__restrict__ U, V2<T> *__restrict__ out,
                                                      T rho, T wp, V2<T> *__restrict__ Cst = nullptr) {

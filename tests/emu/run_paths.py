@@ -183,6 +183,18 @@ def path_launch_form():
     E._ctx = saved
 
 
+def path_stout_form():
+    """The kernel of a stout step, by the rounds of 256 blocks that either would take."""
+    launches = E.lib().emu_launches
+    for L, blocks in (((4, 4, 4, 4), (False, False)), ((2, 2, 2, 66), (False, True)), ((2, 2, 2, 258), (True, True))):
+        for prec in (0, 1):
+            U = rounded(field(L, 2260, 1), prec)
+            before = launches(b"k_smear_stout")
+            got = E.host_links(E.smear(E.links(U, prec), 0.1, 1.0, 1))
+            assert launches(b"k_smear_stout") - before == blocks[prec == 0], (L, prec)
+            assert np.abs(got - O.smear(U, 0.1, 1.0, 1)).max() < (1e-14 if prec == 0 else 1e-6), (L, prec)
+
+
 def path_backward_workspace():
     """The gradient's smallest workspace, as mcg.h states it: ceil(n/c) - 1 + (c - 1) + 5 fields."""
     L, n, c = (4, 4, 4, 16), 3, 1  # 7 fields of 590 kB
