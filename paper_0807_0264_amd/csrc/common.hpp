@@ -367,23 +367,36 @@ template <int TL = 128, int TG = 8> __device__ __forceinline__ int gather_site(c
 }
 // The kernels that read G at a site and its forward neighbours (gauge transform, projection, vortex
 // fields; one thread per half index, both parities) take the same tiles with 256 lanes, each XCD a
-// contiguous range of them, and let the links, touched once, pass by with streaming accesses: more
-// of the neighbours' G then comes from L2.  (Both parities of a tile in the two halves of a block
-// read fewer bytes, 1.35 instead of 1.52 GB for a 32^3x64 projection of 0.91, but took 263 us instead
-// of 228.)
+// contiguous range of them: more of the neighbours' G then comes from L2.  (Both parities of a tile in
+// the two halves of a block read fewer bytes, 1.35 instead of 1.52 GB for a 32^3x64 projection of 0.91,
+// but took 263 us instead of 228.)
 // Slices of fewer than 2048 half-sites (295 KB of G per parity) fit an L2 several times over as they
-// are, and would leave too many lanes of their last tile idle; they stay lexicographic.
+// are, and would leave too many lanes of their last tile idle; they stay lexicographic, and so does a
+// launch without G, which reads no neighbours (32^3x64 projection, FP64: 82.7 against 88.6 us).
 __host__ __device__ inline bool site_tiled(const Geom &g) { return g.Vh / g.L[3] >= 2048; }
-__host__ __device__ inline int site_blocks(const Geom &g) {
-  return site_tiled(g) ? gather_tiles<256>(g) : (g.Vh + 255) / 256;
-}
-// the half-site of this thread in a launch of site_blocks(g) blocks of 256, or -1
-__device__ __forceinline__ int site_of_block(const Geom &g) {
+inline int site_blocks(const Geom &g, bool tiled) { return tiled ? gather_tiles<256>(g) : (g.Vh + 255) / 256; }
+// the most blocks that either order takes
+inline int site_blocks(const Geom &g) { return site_blocks(g, site_tiled(g)); }
+// the half-site of this thread in a launch of site_blocks(g, tiled) blocks of 256, or -1
+__device__ __forceinline__ int site_of_block(const Geom &g, int tiled) {
   const int tile = xcd_range((int)blockIdx.x, (int)gridDim.x);
-  if (site_tiled(g)) return gather_site<256>(g, tile, (int)threadIdx.x);
+  if (tiled) return gather_site<256>(g, tile, (int)threadIdx.x);
   const int h = tile * 256 + (int)threadIdx.x;
   return h < g.Vh ? h : -1;
 }
+// Which of such a launch's link accesses stream past the caches: those of a field that the last-level
+// cache (256 MB) cannot hold beside what else the launch touches.  Loads, where links and G read exceed
+// it; stores, where these and the links written do.  Smaller fields are left there, for the loads that
+// find them there now and for whatever reads the result next.  us, ordinary (loads streaming, stores
+// streaming, both), gauge transform: 14^4 FP64 33 (47, 29, 34), 16^3x32 FP32 20 (24, 20, 27) and FP64 41 (56,
+// 37, 58), 20^3x40 FP32 54 (57, 50, 56) and FP64 101 (92, 80, 94), 24^3x48 FP32 119 (114, 115, 111) and FP64
+// 208 (196, 195, 188), 32^3x64 FP32 360 (352, 350, 333).
+constexpr size_t LLC_BYTES = (size_t)256 << 20;
+struct Streaming {
+  bool loads, stores;
+};
+inline Streaming streaming(size_t read, size_t written) { return {read > LLC_BYTES, read + written > LLC_BYTES}; }
+
 __device__ __forceinline__ int lex_index(const Geom &g, const int c[4]) {
   return c[0] + g.L[0] * (c[1] + g.L[1] * (c[2] + g.L[2] * c[3]));
 }
@@ -479,6 +492,15 @@ template <typename T> struct Links {
   __device__ __forceinline__ M3<T> load(int mu, int par, int h) const { return load_off(mu, off(par, h)); }
   __device__ __forceinline__ void store(int mu, int par, int h, const M3<T> &m) const {
     store_off(mu, off(par, h), m);
+  }
+  // ordinary or streaming
+  template <bool STREAM> __device__ __forceinline__ M3<T> load_as(int mu, int par, int h) const {
+    if constexpr (STREAM) return load_stream(mu, par, h);
+    else return load(mu, par, h);
+  }
+  template <bool STREAM> __device__ __forceinline__ void store_as(int mu, int par, int h, const M3<T> &m) const {
+    if constexpr (STREAM) store_stream(mu, par, h, m);
+    else store(mu, par, h, m);
   }
   // streaming forms, for links touched once next to data that should stay in the caches
   __device__ __forceinline__ M3<T> load_stream(int mu, int par, int h) const {

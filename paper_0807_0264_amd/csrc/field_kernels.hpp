@@ -116,10 +116,11 @@ __global__ __launch_bounds__(256) void k_gauge_op(Geom g, double2 *G, int what) 
   }
 }
 
-template <typename T>
+// LD, ST: the links' loads and stores stream (streaming())
+template <typename T, bool LD, bool ST>
 __global__ __launch_bounds__(256) void k_apply_gauge(Geom g, const V2<T> *U, const double2 *__restrict__ G,
-                                                     V2<T> *out) {
-  const int h = site_of_block(g);
+                                                     V2<T> *out, int tiled) {
+  const int h = site_of_block(g, tiled);
   if (h < 0) return;
   const Links<T> Ui{const_cast<V2<T> *>(U), g.Vh}, O{out, g.Vh};
   const Gauge gg{const_cast<double2 *>(G), g.Vh};
@@ -132,8 +133,8 @@ __global__ __launch_bounds__(256) void k_apply_gauge(Geom g, const V2<T> *U, con
       int e[4];
       moved(g, c, mu, +1, e);
       const M3<double> Gn = gg.load(1 - par, half_index(g, e));
-      const M3<double> u = m_cvt<double>(Ui.load_stream(mu, par, h));
-      O.store_stream(mu, par, h, m_cvt<T>(mul_nd(mul(Gx, u), Gn)));
+      const M3<double> u = m_cvt<double>(Ui.template load_as<LD>(mu, par, h));
+      O.template store_as<ST>(mu, par, h, m_cvt<T>(mul_nd(mul(Gx, u), Gn)));
     }
   }
 }

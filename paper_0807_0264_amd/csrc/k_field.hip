@@ -41,7 +41,15 @@ hipError_t launch_gauge_reunit(const Geom &g, double *G, hipStream_t s) {
 }
 template <typename T>
 hipError_t launch_apply_gauge(const Geom &g, const void *U, const double *G, void *out, hipStream_t s) {
-  k_apply_gauge<T><<<site_blocks(g), 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, (V2<T> *)out);
+  const size_t links = (size_t)g.V * 36 * sizeof(V2<T>), transform = (size_t)g.V * 9 * sizeof(double2);
+  const Streaming st = streaming(links + transform, links);
+  const int tiled = site_tiled(g);
+#define MCG_AG(LD, ST)                                                                                          \
+  k_apply_gauge<T, LD, ST><<<site_blocks(g), 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, (V2<T> *)out, tiled)
+  if (st.loads) MCG_AG(true, true);
+  else if (st.stores) MCG_AG(false, true);
+  else MCG_AG(false, false);
+#undef MCG_AG
   return hipGetLastError();
 }
 template <typename T>

@@ -14,8 +14,18 @@ namespace mcg {
 template <typename T>
 hipError_t launch_vortex_field(const Geom &g, const void *U, const double *G, const int8_t *Z, int mode, void *out,
                                hipStream_t s) {
-  k_vortex_field<T><<<site_blocks(g), 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, Z, mode,
-                                                      (V2<T> *)out);
+  const size_t links = (size_t)g.V * 36 * sizeof(V2<T>), transform = G ? (size_t)g.V * 9 * sizeof(double2) : 0;
+  // Centres alone are written, not read: ordinary stores up to twice the cache, 20^3x40 FP32 15 us (18
+  // streaming), 24^3x48 28 (38), 32^4 48 (59), FP64 24^3x48 76 (77); then 32^4 FP64 111 (107), 32^3x64 FP32
+  // 116 (113) and FP64 228 (220)
+  const Streaming st = mode == 0 ? Streaming{false, links > 2 * LLC_BYTES} : streaming(links + transform, links);
+  const int tiled = mode != 0 && G && site_tiled(g), nb = site_blocks(g, tiled);
+#define MCG_VF(LD, ST)                                                                                           \
+  k_vortex_field<T, LD, ST><<<nb, 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, Z, mode, (V2<T> *)out, tiled)
+  if (st.loads) MCG_VF(true, true);
+  else if (st.stores) MCG_VF(false, true);
+  else MCG_VF(false, false);
+#undef MCG_VF
   return hipGetLastError();
 }
 

@@ -15,8 +15,14 @@ namespace mcg {
 template <typename T>
 hipError_t launch_center_project(const Geom &g, const void *U, const double *G, int8_t *Z,
                                  double *part, double *min_out, hipStream_t s) {
-  const int nb = site_blocks(g), pairs = ((uintptr_t)Z & 1) == 0;
-  k_center_project<T><<<nb, 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, Z, part, pairs);
+  const size_t links = (size_t)g.V * 36 * sizeof(V2<T>);
+  const size_t read = G ? links + (size_t)g.V * 9 * sizeof(double2) : links / 3;
+  const int tiled = G && site_tiled(g), nb = site_blocks(g, tiled), pairs = ((uintptr_t)Z & 1) == 0;
+#define MCG_CP(LD) \
+  k_center_project<T, LD><<<nb, 256, 0, s>>>(g, (const V2<T> *)U, (const double2 *)G, Z, part, pairs, tiled)
+  if (streaming(read, 0).loads) MCG_CP(true);
+  else MCG_CP(false);
+#undef MCG_CP
   k_min_final<<<1, 1024, 0, s>>>(part, nb, min_out);
   return hipGetLastError();
 }

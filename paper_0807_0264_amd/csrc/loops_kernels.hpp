@@ -31,12 +31,12 @@ __device__ __forceinline__ cx<double> center_elem(int m) {
 // mode 0: out_mu(x) = z(m_mu(x)) 1; mode 1: out_mu(x) = conj(z(m_mu(x))) G(x) U_mu(x) G(x+mu)^dag
 // (G may be null: identity).  One thread per half index h, both parities.  out may alias U: every
 // element is read and written by the same thread.  Bound by HBM (mode 1: U, G and Z read and a field
-// written, 724 bytes per site with FP32 links): 32^3x64 425 us with lexicographic tiles, 330 us with
-// site_of_block's and streaming links.
-template <typename T>
+// written, 724 bytes per site with FP32 links): 32^3x64 425 us with lexicographic tiles, 322 us with
+// site_of_block's and streaming links.  LD, ST: loads and stores of links stream (streaming()).
+template <typename T, bool LD, bool ST>
 __global__ __launch_bounds__(256) void k_vortex_field(Geom g, const V2<T> *U, const double2 *__restrict__ G,
-                                                      const int8_t *__restrict__ Z, int mode, V2<T> *out) {
-  const int h = site_of_block(g);
+                                                      const int8_t *__restrict__ Z, int mode, V2<T> *out, int tiled) {
+  const int h = site_of_block(g, tiled);
   if (h < 0) return;
   const Links<T> L{const_cast<V2<T> *>(U), g.Vh};
   const Links<T> O{out, g.Vh};
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256) void k_vortex_field(Geom g, const V2<T> *U, co
         r = m_zero<double>();
         r.e[0] = r.e[4] = r.e[8] = z;
       } else {
-        const M3<double> u = m_cvt<double>(L.load_stream(mu, par, h));
+        const M3<double> u = m_cvt<double>(L.template load_as<LD>(mu, par, h));
         if (G) {
           int e[4];
           moved(g, c, mu, +1, e);
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) void k_vortex_field(Geom g, const V2<T> *U, co
 #pragma unroll
         for (int k = 0; k < 9; k++) r.e[k] = r.e[k] * zc;
       }
-      O.store_stream(mu, par, h, m_cvt<T>(r));
+      O.template store_as<ST>(mu, par, h, m_cvt<T>(r));
     }
   }
 }

@@ -9,11 +9,14 @@ namespace mcg {
 // go out in one store.  min_margin partials: one per block, in any order.  Bound by HBM: U and G once
 // and Z written, 436 bytes per site (FP32 links).  32^3x64: 307 us with lexicographic tiles and byte
 // stores, 228 us now (1.52 GB read, at the rate of the last-level cache).
-template <typename T>
+// LD: the links' loads stream (streaming(); 16^3x32 FP32 17.9 us without, 19.8 with; without G, when the
+// links' diagonals alone are read, 32^3x64 FP32 60 and 75).
+template <typename T, bool LD>
 __global__ __launch_bounds__(256) void k_center_project(Geom g, const V2<T> *__restrict__ U,
                                                         const double2 *__restrict__ G,
-                                                        int8_t *__restrict__ Z, double *part, int pairs) {
-  const int h = site_of_block(g);
+                                                        int8_t *__restrict__ Z, double *part, int pairs,
+                                                        int tiled) {
+  const int h = site_of_block(g, tiled);
   double mmin = 10.0;
   if (h >= 0) {
     const Links<T> L{const_cast<V2<T> *>(U), g.Vh};
@@ -28,7 +31,7 @@ __global__ __launch_bounds__(256) void k_center_project(Geom g, const V2<T> *__r
       if (G) Gx = gg.load(par, h);
 #pragma unroll
       for (int mu = 0; mu < 4; mu++) {
-        const M3<double> u = m_cvt<double>(L.load_stream(mu, par, h));
+        const M3<double> u = m_cvt<double>(L.template load_as<LD>(mu, par, h));
         cx<double> t;
         if (G) {
           int e[4];

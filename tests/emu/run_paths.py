@@ -195,6 +195,23 @@ def path_stout_form():
             assert np.abs(got - O.smear(U, 0.1, 1.0, 1)).max() < (1e-14 if prec == 0 else 1e-6), (L, prec)
 
 
+def path_field_accesses():
+    """Small fields stay in the caches: gauge transform, projection and vortex fields of them run the
+    kernels with ordinary accesses."""
+    launches = E.lib().emu_launches
+    U, G = E.links(field((4, 4, 4, 4), 2270, 1), 1), E.gauge(S.haar_gauge((4, 4, 4, 4), S.sub_seed(2271)))
+    Z, _ = E.center_project(U, G)
+    for name, run in ((b"k_apply_gauge<T, false, false>", lambda: E.apply_gauge(U, G)),
+                      (b"k_center_project<T, false>", lambda: E.center_project(U, G)),
+                      (b"k_center_project<T, false>", lambda: E.center_project(U, None)),
+                      (b"k_vortex_field<T, false, false>", lambda: E.vortex_field(U, G, Z, 0)),
+                      (b"k_vortex_field<T, false, false>", lambda: E.vortex_field(U, G, Z, 1)),
+                      (b"k_vortex_field<T, false, false>", lambda: E.vortex_field(U, None, Z, 1))):
+        before = launches(name)
+        run()
+        assert launches(name) == before + 1, name
+
+
 def path_backward_workspace():
     """The gradient's smallest workspace, as mcg.h states it: ceil(n/c) - 1 + (c - 1) + 5 fields."""
     L, n, c = (4, 4, 4, 16), 3, 1  # 7 fields of 590 kB
