@@ -464,7 +464,7 @@ mcg_status mcg_wilson_loops(mcg_ctx *ctx, const mcg_field *U, int32_t nvec, cons
  * + 5 fields of U's size (the checkpoints after U itself, one segment's fields,
  * and staple sums); if that cannot be allocated (or exceeds
  * MCG_OPT_SCRATCH_LIMIT_MIB), k - 1 + (c - 1) + 5 fields, the staples then
- * formed again in the adjoint (the same results, more time). */
+ * formed again in the adjoint (the same results to rounding, more time). */
 mcg_status mcg_smear_mcg_backward(mcg_ctx *ctx, const mcg_field *U, double rho, double eps,
                                   int32_t n, const mcg_gauge *Gstar, int32_t ckpt_every,
                                   mcg_field *gradU, double *loss, double *dRho, double *dEps,

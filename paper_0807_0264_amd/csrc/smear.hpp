@@ -201,10 +201,12 @@ __device__ __forceinline__ void staples(const Geom &g, const Links<T> &L, int pa
   if constexpr (!OI) {
     // Stout, for small launches and for the adjoint where the forward pass's staple sums did not fit:
     // the six links of a direction are loaded together and (FP32) held until all six are in, so a wave
-    // has six loads in flight instead of three.  The directions are taken as mu ^ 1, mu ^ 2, mu ^ 3, the
-    // order of k_smear_stout.
-    for (int j = 1; j < 4; j++) {
-      const int nu = mu ^ j;
+    // has six loads in flight instead of three.  Unrolled, nu is known when the kernel is compiled and a
+    // direction's offsets need no look-up of its extent: k_smear, 4^4 FP32 9.3 -> 8.7 us, 8^4 9.6 -> 8.9,
+    // FP64 10.6 -> 9.4, against directions taken as mu ^ 1, mu ^ 2, mu ^ 3 in a loop.
+#pragma unroll
+    for (int nu = 0; nu < 4; nu++) {
+      if (nu == mu) continue;
       const Around<T> x = opaque_site(x0);
       const int n1 = move_by<T>(g, c, nu, +1), n_1 = move_by<T>(g, c, nu, -1);
       M3<T> unu_x = L.load_off(nu, x.even(0)), umu_xpn = L.load_off(mu, x.odd(n1)),

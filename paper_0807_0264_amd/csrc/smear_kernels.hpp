@@ -10,7 +10,7 @@ namespace mcg {
 // (stout_in_blocks).  CS = 1: also store the staple sums Cp (and Cr, OI) of every link in Cst, as two link
 // fields [Cp | Cr], for the adjoint's first pass
 template <typename T, bool OI, int CS = 0>
-__global__ __launch_bounds__(128, sizeof(T) == 4 ? 2 : 1) void k_smear(Geom g, const V2<T> *__restrict__ U,
+__global__ __launch_bounds__(128, sizeof(T) == 4 ? (OI ? 2 : 3) : 1) void k_smear(Geom g, const V2<T> *__restrict__ U,
                                                V2<T> *__restrict__ out, T rho, T wp, T wr,
                                                V2<T> *__restrict__ Cst = nullptr) {
   // one block per (tile, direction, parity), the tiles as gather_site lays them out; the eight blocks
@@ -44,10 +44,11 @@ __global__ __launch_bounds__(128, sizeof(T) == 4 ? 2 : 1) void k_smear(Geom g, c
 // other through LDS, so that a link takes 13 matrices from the caches instead of 19 (11.5 GB per
 // 32^3x64 FP32 step, 14 TB/s, was what the step had waited for).  FP32 runs four waves per SIMD (126
 // registers), and tiles in groups of four t-slices, the 64-site tiles of eight being more than an
-// XCD's L2 holds.  CS = 1: also store Cp in Cst; the sums in the order of staples<T, false>.
+// XCD's L2 holds.  CS = 1: also store Cp in Cst.
 // 32^3x64 FP32, per step: 0.802 ms with a wave per link and 19 loads, 0.767 with the exchange at three
 // waves per SIMD, 0.747 at four, 0.713 with the groups of four (of two: 0.744): 76 % of the VALU issue
-// rate.  FP64, 20^3x40 and 16^4: 0.136 -> 0.123 ms on average.  Same bits as k_smear<T, false>.
+// rate.  FP64, 20^3x40 and 16^4: 0.136 -> 0.123 ms on average.  The sums
+// of k_smear<T, false>, in another order.
 template <typename T, int CS = 0>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void k_smear_stout(Geom g, const V2<T> *__restrict__ U, V2<T> *__restrict__ out,
                                                      T rho, T wp, V2<T> *__restrict__ Cst = nullptr) {
