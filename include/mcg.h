@@ -443,11 +443,11 @@ mcg_status mcg_vortex_field(mcg_ctx *ctx, const mcg_field *U, const mcg_gauge *G
  * 0 < |v|_1 <= 24 with |v_j| <= 8, and rmax * max_j |v_j| <= min(L[0], L[1],
  * L[2]); sums in FP64, deterministic.  Synchronises the stream.
  * Where every time link is unitary to rounding (each entry of U_3 U_3^dagger - 1
- * below 2.4e-7 with FP32 links, 2.5e-15 with FP64) the loops are formed in the
- * temporal gauge of the links' unitary parts, which leaves out at most T times
- * that of W(R, T) if all time links are off by the same scale, and what does
- * not average out over the sites otherwise; any other links are multiplied
- * out as they are, which takes several times as long. */
+ * below 2.4e-7 with FP32 links, 1e-14 with FP64) the loops are formed in the
+ * temporal gauge of the links' unitary parts, with the scale that the time
+ * links have in common; any other links are multiplied out as they are, which
+ * takes several times as long (FP32 fields are beyond this after one smearing
+ * step, FP64 fields after about a hundred). */
 mcg_status mcg_wilson_loops(mcg_ctx *ctx, const mcg_field *U, int32_t nvec, const int32_t *vec,
                             int32_t rmax, int32_t tmax, double *W, void *stream);
 

@@ -131,10 +131,11 @@ struct WlPlan {
   int TE, own, nseg, nw, nblk;
 };
 template <typename T> WlPlan wl_plan(const Geom &g, int tmax);
-// the transform to the gauge into H (TE * 9 * Vs complex double); *bad (host memory) is set where a time
-// link is not unitary
+// the transform to the gauge into H (TE * 9 * Vs complex double), and sums of tr(U_3 U_3^dag - 1) into dev
+// (wl_gauge_blocks(g) doubles); *bad (host memory) is set where a time link is not unitary
+int wl_gauge_blocks(const Geom &g);
 template <typename T>
-hipError_t launch_wl_gauge(const Geom &g, const void *U, void *H, int TE, int *bad, hipStream_t s);
+hipError_t launch_wl_gauge(const Geom &g, const void *U, void *H, int TE, double *dev, int *bad, hipStream_t s);
 // the spatial links in the gauge into N (3 * TE * 9 * Vs complex of T)
 template <typename T>
 hipError_t launch_wl_links(const Geom &g, const void *U, const void *H, void *N, int TE, hipStream_t s);
@@ -142,7 +143,7 @@ hipError_t launch_wl_links(const Geom &g, const void *U, const void *H, void *N,
 // A holds imgs.n * TE * 9 * Vs complex of T, part imgs.n * rmax * tmax * plan.nblk doubles
 template <typename T>
 hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs, const WlPlan &plan,
-                           int rmax, int tmax, void *A, double *part, double *res, hipStream_t s);
+                           int rmax, int tmax, void *A, double *part, const double *dev, double *res, hipStream_t s);
 template <typename T>
 hipError_t launch_vortex_field(const Geom &g, const void *U, const double *G, const int8_t *Z, int mode, void *out,
                                hipStream_t s);

@@ -68,10 +68,10 @@ template <typename T> WlPlan wl_plan(const Geom &g, int tmax) {
   return p;
 }
 
+int wl_gauge_blocks(const Geom &g) { return (g.L[0] * g.L[1] * g.L[2] + 63) / 64; }
 template <typename T>
-hipError_t launch_wl_gauge(const Geom &g, const void *U, void *H, int TE, int *bad, hipStream_t s) {
-  const int Vs = g.L[0] * g.L[1] * g.L[2];
-  k_wl_gauge<T><<<(Vs + 63) / 64, 64 * WL_WAVES, 0, s>>>(g, (const V2<T> *)U, (double2 *)H, TE, bad);
+hipError_t launch_wl_gauge(const Geom &g, const void *U, void *H, int TE, double *dev, int *bad, hipStream_t s) {
+  k_wl_gauge<T><<<wl_gauge_blocks(g), 64 * WL_WAVES, 0, s>>>(g, (const V2<T> *)U, (double2 *)H, TE, dev, bad);
   return hipGetLastError();
 }
 template <typename T>
@@ -83,7 +83,7 @@ hipError_t launch_wl_links(const Geom &g, const void *U, const void *H, void *N,
 
 template <typename T>
 hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs, const WlPlan &plan,
-                           int rmax, int tmax, void *A, double *part, double *res, hipStream_t s) {
+                           int rmax, int tmax, void *A, double *part, const double *dev, double *res, hipStream_t s) {
   const int Vs = g.L[0] * g.L[1] * g.L[2];
   const dim3 gl(plan.TE * ((Vs + 255) / 256), imgs.n), gc(plan.nblk, imgs.n);
   k_wl_line<T><<<gl, 256, 0, s>>>(g, (const V2<T> *)N, imgs, plan.TE, (V2<T> *)A);
@@ -108,7 +108,7 @@ hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs,
   else MCG_WL_RANGE(16, 13, 1 << 16);
 #undef MCG_WL_RANGE
 #undef MCG_WL
-  k_wl_final<<<rmax * tmax, 256, 0, s>>>(part, plan.nblk, imgs, rmax * tmax, res);
+  k_wl_final<<<rmax * tmax, 256, 0, s>>>(part, plan.nblk, imgs, rmax * tmax, tmax, dev, wl_gauge_blocks(g), 1.0 / (6.0 * g.V), res);
   return hipGetLastError();
 }
 
@@ -119,10 +119,10 @@ hipError_t launch_wl_loops(const Geom &g, const void *N, const LoopImages &imgs,
   template hipError_t launch_wloops<T>(const Geom &, const void *, const LoopImage<T> *, int, int, int, double *, \
                                        double *, hipStream_t);                                             \
   template WlPlan wl_plan<T>(const Geom &, int);                                                           \
-  template hipError_t launch_wl_gauge<T>(const Geom &, const void *, void *, int, int *, hipStream_t);     \
+  template hipError_t launch_wl_gauge<T>(const Geom &, const void *, void *, int, double *, int *, hipStream_t); \
   template hipError_t launch_wl_links<T>(const Geom &, const void *, const void *, void *, int, hipStream_t); \
   template hipError_t launch_wl_loops<T>(const Geom &, const void *, const LoopImages &, const WlPlan &, int, int, \
-                                         void *, double *, double *, hipStream_t);
+                                         void *, double *, const double *, double *, hipStream_t);
 MCG_LOOPS_INST(float)
 MCG_LOOPS_INST(double)
 

@@ -189,15 +189,16 @@ __global__ __launch_bounds__(256) void k_zero(double *p, int n) {
 // Fields in this form are [t][element][s] complex, s = x + Lx (y + Ly z), t < Lt + tmax.
 
 // Largest |(U_3 U_3^dag - 1)_ij| (real and imaginary parts) accepted.  The gauge takes each time link's
-// unitary part, where the general path multiplies the link as it is: links that all deviate alike by a
-// scale shift W(R, T) by T times this, and nothing averages that away.  So it is no more than the roundings
-// of a link that was unitary: a unitary matrix rounded to FP32 is off by at most 2^-23 (1.0e-7 in thermalised
-// 32^3x64 fields), its gauge transform or its vortex removal rounded once more by at most 2^-22 (1.7e-7);
-// the same fields in FP64 are off by 1.1e-15 and 2.0e-15.  One FP32 smearing step already leaves 4e-7, ten
-// 1.2e-6: smeared FP32 fields take the general path.
+// unitary part, where the general path multiplies the link as it is.  The scale that all time links have
+// in common is put back (k_wl_final); what is left out is how a link's own deviation goes with the loops
+// it is in, and that no sum over sites averages away.  The lines lie where it stays below what the
+// general path rounds away: largest error of W(R <= 3, T <= 10) at 20^3x40 against 64-bit mathematics, gauged
+// and general, FP32 fields as given (off by 1.0e-7, transformed or vortex-removed ones by 1.7e-7) 8e-11
+// and 1.1e-10, after one smearing step (4e-7) 1.4e-10 and 1.1e-10, after ten (1.2e-6) 8e-10 and 1.3e-10; FP64
+// fields (1.1e-15) and after 80 smearing steps (8e-15) 1-3e-16 both ways.
 template <typename T> struct WlTol;
 template <> struct WlTol<float> { static constexpr double v = 2.4e-7; };
-template <> struct WlTol<double> { static constexpr double v = 2.5e-15; };
+template <> struct WlTol<double> { static constexpr double v = 1e-14; };
 // R: the slices of S_k that a wave holds in registers; Q: the slices t whose loops it sums (all read
 // from LDS, so that every wave of a block has a share).  With these a wave needs at most 256 registers (two waves per SIMD).
 template <typename T> struct WlTile;
@@ -239,13 +240,14 @@ __device__ __forceinline__ void wl_site(const Geom &g, int s, int c[4]) {
 }
 __device__ __forceinline__ int wl_index(const Geom &g, const int c[4]) { return c[0] + g.L[0] * (c[1] + g.L[1] * c[2]); }
 
-// h in FP64, 64 spatial sites per block.  U_3 is brought to unitarity in FP64 first (one Newton step
-// of the polar decomposition), so h stays unitary to FP64 rounding however far it runs.  The chain of
-// products along t is cut into WL_WAVES pieces: each wave multiplies its piece out, takes the
-// pieces before it from LDS and goes through its piece again (50 slices: 59 us as one chain).
+// h in FP64, 64 spatial sites per block.  Each product h U_3 is brought back to unitarity by one Newton
+// step of the polar decomposition, so h stays unitary to FP64 rounding however far it runs, and what U_3
+// itself is off by, which is measured there, is left out.  The chain of products along t is cut into
+// WL_WAVES pieces: each wave multiplies its piece out, takes the pieces before it from LDS and goes
+// through its piece again (50 slices: 59 us as one chain).
 template <typename T>
 __global__ __launch_bounds__(64 * WL_WAVES) void k_wl_gauge(Geom g, const V2<T> *__restrict__ U,
-                                                           double2 *__restrict__ H, int TE, int *bad_out) {
+                                                           double2 *__restrict__ H, int TE, double *__restrict__ dev, int *bad_out) {
   __shared__ double2 piece[WL_WAVES - 1][9][64];
   const int Vs = g.L[0] * g.L[1] * g.L[2];
   const int lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6);
@@ -257,24 +259,26 @@ __global__ __launch_bounds__(64 * WL_WAVES) void k_wl_gauge(Geom g, const V2<T> 
   const int p0 = (c[0] + c[1] + c[2]) & 1, Sh = Vs >> 1, n = (TE + WL_WAVES - 1) / WL_WAVES;
   const int lo = wave * n < TE ? wave * n : TE, hi = lo + n < TE ? lo + n : TE;
   bool bad = false;
+  double tr = 0.0, off = 0.0;  // tr(U U^dag - 1) of the last link; of the block's own links
   auto link = [&](int te) -> M3<T> {
     const int t = te % g.L[3];
     return L.load(3, (p0 + t) & 1, t * Sh + (s >> 1));
   };
-  auto unitary = [&](const M3<T> &v) -> M3<double> {
-    const M3<double> u = m_cvt<double>(v);
-    M3<double> q = mul_nd(u, u);  // U U^dag; then (3 - U U^dag) / 2
+  // the unitary part of m: (3 - m m^dag) / 2 m
+  auto unitary = [&](const M3<double> &m) -> M3<double> {
+    M3<double> q = mul_nd(m, m);
+    tr = (q.e[0].re - 1.0) + (q.e[4].re - 1.0) + (q.e[8].re - 1.0);
 #pragma unroll
     for (int k = 0; k < 9; k++) {
       const double one = k % 4 == 0 ? 1.0 : 0.0;
       bad = bad || !(fabs(q.e[k].re - one) <= WlTol<T>::v) || !(fabs(q.e[k].im) <= WlTol<T>::v);
       q.e[k] = cx<double>{1.5 * one - 0.5 * q.e[k].re, -0.5 * q.e[k].im};
     }
-    return mul(q, u);
+    return mul(q, m);
   };
   M3<double> h = m_ident<double>();
   if (wave < WL_WAVES - 1) {
-    for (int te = lo; te < hi; te++) h = mul(h, unitary(link(te)));
+    for (int te = lo; te < hi; te++) h = unitary(mul(h, m_cvt<double>(link(te))));
 #pragma unroll
     for (int k = 0; k < 9; k++) piece[wave][k][lane] = make_double2(h.e[k].re, h.e[k].im);
   }
@@ -289,11 +293,15 @@ __global__ __launch_bounds__(64 * WL_WAVES) void k_wl_gauge(Geom g, const V2<T> 
     }
     h = mul(h, p);
   }
+  h = unitary(h);
   for (int te = lo; te < hi; te++) {
     const M3<T> u = link(te);
     if (live) wl_store(H, te, Vs, (unsigned)s * 16u, h);
-    h = mul(h, unitary(u));
+    h = unitary(mul(h, m_cvt<double>(u)));
+    if (live && te < g.L[3]) off += tr;
   }
+  off = block_sum<64 * WL_WAVES>(off);
+  if (threadIdx.x == 0) dev[blockIdx.x] = off;
   if (bad) *bad_out = 1;  // the same value from every lane
 }
 
@@ -493,17 +501,21 @@ __global__ __launch_bounds__(64 * NW, 2) void k_wl_corr(Geom g, const V2<T> *__r
 }
 
 // res[i] += sum over the images of weight * sum over the blocks of part, i = (k - 1) tmax + T - 1: one
-// block per i, terms in a fixed order
+// block per i, terms in a fixed order.  The 2 T time links of a loop carry the mean scale that the gauge
+// left out, 1 + norm * sum of dev.
 __global__ __launch_bounds__(256) void k_wl_final(const double *__restrict__ part, int nb, LoopImages imgs, int nres,
+                                                  int tmax, const double *__restrict__ dev, int ndev, double norm,
                                                   double *res) {
-  double v = 0.0;
+  double v = 0.0, e = 0.0;
+  for (int b = threadIdx.x; b < ndev; b += 256) e += dev[b];
+  e = block_sum<256>(e);
   for (int i = 0; i < imgs.n; i++) {
     const double *p = part + ((size_t)i * nres + blockIdx.x) * nb;
     const double w = imgs.img[i].weight;
     for (int b = threadIdx.x; b < nb; b += 256) v += w * p[b];
   }
   v = block_sum<256>(v);
-  if (threadIdx.x == 0) res[blockIdx.x] += v;
+  if (threadIdx.x == 0) res[blockIdx.x] += v * exp(2.0 * (blockIdx.x % tmax + 1) * log1p(norm * e));
 }
 
 }  // namespace mcg

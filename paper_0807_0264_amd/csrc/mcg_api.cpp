@@ -2003,7 +2003,8 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
   const int nres = nvec * rmax * tmax;
   // the transform is needed before the first line
   auto lines_of = [&](int n) { return up(std::max(hbytes, abytes * n)); };
-  auto need = [&](int n) { return up(3 * abytes) + lines_of(n) + pbytes * n; };
+  const size_t dbytes = up(sizeof(double) * wl_gauge_blocks(g));
+  auto need = [&](int n) { return up(3 * abytes) + lines_of(n) + dbytes + pbytes * n; };
   const size_t held = general_scratch<T>(g, tmax).total;
   int ni = LOOP_IMAGES_PER_LAUNCH;
   while (ni > 1 && need(ni) > held) ni--;
@@ -2024,12 +2025,12 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
     }
   } give_back{ctx, lend};
   char *links = (char *)ctx->wl_lines.p, *lines = links + up(3 * abytes);
-  double *part = (double *)(lines + lines_of(ni));
+  double *dev = (double *)(lines + lines_of(ni)), *part = (double *)((char *)dev + dbytes);
   mcg_status st;
   if ((st = ensure_results(ctx))) return st;
   int *bad = (int *)ctx->h_res;
   *bad = 0;
-  HIPCHK(launch_wl_gauge<T>(g, U->ptr, lines, plan.TE, bad, s));
+  HIPCHK(launch_wl_gauge<T>(g, U->ptr, lines, plan.TE, dev, bad, s));
   HIPCHK(hipStreamSynchronize(s));
   if (*bad) return MCG_OK;
   double *res = (double *)ctx->wl_res.p;
@@ -2055,7 +2056,7 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
         // Re tr / 3, averaged over sites and images
         d.weight = (double)e.second / (3.0 * (double)nimg * (double)g.V);
       }
-      HIPCHK(launch_wl_loops<T>(g, links, set, plan, rmax, tmax, lines, part,
+      HIPCHK(launch_wl_loops<T>(g, links, set, plan, rmax, tmax, lines, part, dev,
                                 res + (size_t)i * rmax * tmax, s));
     }
   }
