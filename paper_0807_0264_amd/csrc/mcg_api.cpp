@@ -1878,7 +1878,8 @@ std::vector<int> staircase_steps(const int v[3]) {
 // number of images it stands for: an image whose reversed, negated sequence (the same loop
 // traversed from its other corner, equal in translation-averaged Re tr) is already listed is
 // merged into that entry
-std::vector<std::pair<std::vector<int>, int>> path_images(const std::vector<int> &base) {
+using PathImages = std::vector<std::pair<std::vector<int>, int>>;
+PathImages path_images(const std::vector<int> &base) {
   static const int perms[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
   std::vector<std::vector<int>> all;
   for (const auto &p : perms)
@@ -1892,7 +1893,7 @@ std::vector<std::pair<std::vector<int>, int>> path_images(const std::vector<int>
     }
   std::sort(all.begin(), all.end());
   all.erase(std::unique(all.begin(), all.end()), all.end());
-  std::vector<std::pair<std::vector<int>, int>> out;
+  PathImages out;
   for (const auto &img : all) {
     std::vector<int> rn(img.rbegin(), img.rend());
     for (int &x : rn) x = -x;
@@ -1923,11 +1924,31 @@ template <typename T> LoopScratch general_scratch(const Geom &g, int tmax) {
   return r;
 }
 
+// The images of each direction's path, formed when first asked for (microseconds of host time each, behind
+// the kernels already launched)
+class Paths {
+  const int32_t *vec_;
+  std::vector<PathImages> done_;
+
+ public:
+  const int n;
+  Paths(int nvec, const int32_t *vec) : vec_(vec), n(nvec) {}
+  const PathImages &operator[](int i) {
+    while ((int)done_.size() <= i) {
+      const int32_t *v = vec_ + 3 * done_.size();
+      const int w[3] = {v[0], v[1], v[2]};
+      done_.push_back(path_images(staircase_steps(w)));
+    }
+    return done_[i];
+  }
+};
+
 // The loops with their time sides multiplied out: any links.
 template <typename T>
-mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t *vec, int rmax, int tmax,
+mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, Paths &paths, int rmax, int tmax,
                           double *W, hipStream_t s) {
   const Geom g = geom_of(U->d);
+  const int nvec = paths.n;
   const int nres = nvec * rmax * tmax;
   const LoopScratch sc = general_scratch<T>(g, tmax);
   const int ni = sc.ni;
@@ -1944,8 +1965,7 @@ mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, int nvec, const int3
   const LoopImage<T> *dI = (const LoopImage<T> *)ctx->wl_img.p;
   HIPCHK(launch_zero(res, nres, s));
   for (int i = 0; i < nvec; i++) {
-    const int v[3] = {vec[3 * i], vec[3 * i + 1], vec[3 * i + 2]};
-    const auto imgs = path_images(staircase_steps(v));
+    const PathImages &imgs = paths[i];
     int nimg = 0;
     for (const auto &e : imgs) nimg += e.second;
     for (size_t c0 = 0; c0 < imgs.size(); c0 += ni) {
@@ -1990,10 +2010,11 @@ mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, int nvec, const int3
 // and leaves it room.  Lattices so large that one image exceeds this (the gauged links are three
 // lines, and the transform, in FP64, shares the image's space) take the buffer for the call only.
 template <typename T>
-mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t *vec, int rmax, int tmax,
+mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, Paths &paths, int rmax, int tmax,
                          double *W, hipStream_t s, bool *done) {
   *done = false;
   const Geom g = geom_of(U->d);
+  const int nvec = paths.n;
   const WlPlan plan = wl_plan<T>(g, tmax);
   if (!plan.ok) return MCG_OK;
   auto up = [](size_t n) { return (n + 255) / 256 * 256; };
@@ -2037,8 +2058,7 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
   HIPCHK(launch_zero(res, nres, s));
   HIPCHK(launch_wl_links<T>(g, U->ptr, lines, links, plan.TE, s));
   for (int i = 0; i < nvec; i++) {
-    const int v[3] = {vec[3 * i], vec[3 * i + 1], vec[3 * i + 2]};
-    const auto imgs = path_images(staircase_steps(v));
+    const PathImages &imgs = paths[i];
     int nimg = 0;
     for (const auto &e : imgs) nimg += e.second;
     for (size_t c0 = 0; c0 < imgs.size(); c0 += ni) {
@@ -2066,12 +2086,35 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32
   return MCG_OK;
 }
 
+// Whether a call asks for so few loops that the gauge, formed once per call, costs more than it saves:
+// microseconds of either path beside what both take.  General: per (direction, k) its launches, a
+// chain of tmax products and the products of all sites.  Gauged: the scan along t, the gauged links, and
+// three launches per direction.  us, general (gauged), FP32: one direction, R = 1, T <= 4: 4^3x16 62 (82),
+// 8^3x64 64 (116), 12^3x64 90 (131); R <= 4: 4^3x64 146 (131), 8^3x96 180 (167), 12^3x64 262 (167); FP64 R = 1,
+// T <= 8: 4^3x32 72 (88), 12^3x48 168 (130).
+template <typename T>
+bool few_loops(const Geom &g, Paths &paths, int rmax, int tmax) {
+  const double product = sizeof(T) == 4 ? 1.8e-5 : 2.8e-5;  // one site's loop, per extent T
+  const double gauged = 30.0 + 0.45 * (g.L[3] + tmax) + 2.5e-4 * g.V + 20.0 * (paths.n - 1);
+  double general = 0.0;
+  for (int i = 0; i < paths.n && general < gauged; i++)
+    general += rmax * (11.0 + 2.2 * tmax + product * g.V * paths[i].size() * (tmax + 2));
+  return general < gauged;
+}
+
 template <typename T>
 mcg_status wilson_impl(mcg_ctx *ctx, const mcg_field *U, int nvec, const int32_t *vec, int rmax, int tmax,
                        double *W, hipStream_t s) {
+  Paths paths(nvec, vec);
+  mcg_status st;
+  const std::string err = ctx->err;
+  if (few_loops<T>(geom_of(U->d), paths, rmax, tmax)) {
+    if ((st = wilson_general<T>(ctx, U, paths, rmax, tmax, W, s)) != MCG_ENOMEM) return st;
+    ctx->err = err;  // the gauge may do with less
+  }
   bool done = false;
-  const mcg_status st = wilson_gauged<T>(ctx, U, nvec, vec, rmax, tmax, W, s, &done);
-  return st || done ? st : wilson_general<T>(ctx, U, nvec, vec, rmax, tmax, W, s);
+  st = wilson_gauged<T>(ctx, U, paths, rmax, tmax, W, s, &done);
+  return st || done ? st : wilson_general<T>(ctx, U, paths, rmax, tmax, W, s);
 }
 
 }  // namespace

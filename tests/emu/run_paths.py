@@ -72,9 +72,22 @@ def path_loops_extents():
         want = O.wilson_loops(U, [(1, 0, 0)], 2, 18)
         for tmax in (1, 4, 5, 8, 9, 10, 11, 12, 13, 16, 17, 18):
             before = E.lib().emu_launches(b"k_wl_corr")
-            got = E.wilson_loops(E.links(U, prec), [(1, 0, 0)], 2, tmax)
-            assert E.lib().emu_launches(b"k_wl_corr") == before + 1, (prec, tmax)
+            n = 4 if tmax < 5 else 1  # directions asked for: so many loops that the gauge pays
+            got = E.wilson_loops(E.links(U, prec), n * [(1, 0, 0)], 2, tmax)
+            assert E.lib().emu_launches(b"k_wl_corr") == before + n, (prec, tmax)
             assert np.abs(got - want[..., :tmax]).max() < (1e-13 if prec == 0 else 2e-6), (prec, tmax)
+
+
+def path_loops_few():
+    """Few loops are multiplied out, without the gauge; many take it."""
+    L = (4, 4, 4, 16)
+    for prec in (0, 1):
+        U = E.links(loop_field(L, 2290, prec), prec)
+        for vecs, rmax, tmax, gauged in (([(1, 0, 0)], 1, 4, False), ([(1, 0, 0)], 4, 4, True),
+                                         (2 * [(1, 0, 0)], 2, 1, False)):
+            before = E.lib().emu_launches(b"k_wl_gauge")
+            E.wilson_loops(U, vecs, rmax, tmax)
+            assert E.lib().emu_launches(b"k_wl_gauge") - before == gauged, (prec, rmax, tmax)
 
 
 def cold_field(L, prec, steps):
@@ -94,7 +107,7 @@ def path_loops_scaled():
     for prec, ulp in ((0, 2.0 ** -52), (1, 2.0 ** -23)):
         for steps in (1, 2, 3, 5, 6, 40, 200):
             U, scale = cold_field(L, prec, steps)
-            got = E.wilson_loops(E.links(U, prec), [(1, 0, 0)], 1, tmax)[0, 0]
+            got = E.wilson_loops(E.links(U, prec), [(1, 0, 0)], 2, tmax)[0, 0]
             for T in range(1, tmax + 1):
                 err = abs(got[T - 1] / scale ** (2 * T) - 1)
                 assert err <= (2 * T + 2) * ulp, (prec, steps, T, err)
@@ -107,9 +120,9 @@ def path_loops_precision():
     L = (4, 4, 2, 58)
     U = field(L, 2255, 3)
     before = E.lib().emu_launches(b"k_wl_corr")
-    got = E.wilson_loops(E.links(U, 0), [(1, 0, 0)], 1, 24)
+    got = E.wilson_loops(E.links(U, 0), [(1, 0, 0)], 2, 24)
     assert E.lib().emu_launches(b"k_wl_corr") == before + 1
-    err = np.abs(got - O.wilson_loops(U, [(1, 0, 0)], 1, 24)).max()
+    err = np.abs(got - O.wilson_loops(U, [(1, 0, 0)], 2, 24)).max()
     assert err <= 5e-16, err
 
 
@@ -155,11 +168,11 @@ def path_loops_refused():
     assert E.lib().mcg_create(C.byref(h), 0) == 0
     assert E.lib().mcg_set_option(h, A.MCG_OPT_SCRATCH_LIMIT_MIB, 4) == 0
     E._ctx = h
-    for bad, status in ((None, A.MCG_OK), (1.001, A.MCG_ENOMEM)):
+    for bad, rmax, status in ((None, 1, A.MCG_OK), (None, 4, A.MCG_OK), (1.001, 4, A.MCG_ENOMEM)):
         U = E.links(rounded(loop_field(L, 2220, 1, bad), 1), 1)
         f = U.abi()
-        W = np.full((1, 1, tmax), 7.0)
-        st = E.lib().mcg_wilson_loops(h, C.byref(f), 1, (C.c_int32 * 3)(1, 0, 0), 1, tmax,
+        W = np.full((1, rmax, tmax), 7.0)
+        st = E.lib().mcg_wilson_loops(h, C.byref(f), 1, (C.c_int32 * 3)(1, 0, 0), rmax, tmax,
                                       W.ctypes.data_as(C.POINTER(C.c_double)), None)
         assert st == status, (st, E.lib().mcg_last_error(h))
         assert (W == 7.0).all() == (bad is not None), W
