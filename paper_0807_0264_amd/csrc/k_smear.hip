@@ -11,17 +11,19 @@
 namespace mcg {
 
 // Whether a stout step runs k_smear_stout (blocks of four waves that read 13 matrices per link) rather
-// than k_smear (blocks of two, 19 matrices).  Small launches are a few rounds of blocks over the 256 CUs:
-// p of k_smear, e of k_smear_stout.  With p = 2e a CU works through as many waves either way and the
-// fewer reads win; with p < 2e the finer blocks leave it fewer waves.  From e = 4 on rounds matter little;
-// in FP32 a single round waits for latency alone, which the barriers of k_smear_stout only lengthen.
+// than k_smear (blocks of two, 19 matrices; one where a slice has no more than 64 half-sites).  Small
+// launches are a few rounds of blocks over the 256 CUs: p of k_smear, e of k_smear_stout.  Where a CU then
+// works through as many waves either way (p = 2e) the fewer reads win; with p < 2e the finer blocks leave
+// it fewer waves.  From e = 4 on rounds matter little; in FP32 a single round waits for latency alone,
+// which the barriers of k_smear_stout only lengthen.
 // us per step, k_smear (k_smear_stout).  FP32: 4^4 8.6 (11.8), 8^4 8.8 (12.0), 12^2 10 6 (p = 2, e = 1) 11.5
 // (13.2), 12^4 (3, 2) 14.4 (15.4), 12^3x16 (4, 2) 16.9 (15.4), 14^4 (5, 3) 19.1 (19.4), 16^3x12 (6, 3) 20.6
 // (20.6), 16^4 (8, 4) 27.5 (23.9).  FP64: 4^4 9.2 (11.0), 8^4 9.4 (12.5), 12^2 10 6 15.6 (14.7), 12^4 16.6
 // (18.7), 12^3x16 20.4 (19.6), 14^4 27.7 (28.6), 16^3x12 29.9 (29.4), 16^4 39.8 (38.2).
 template <typename T> static bool stout_in_blocks(const Geom &g) {
   const int p = (8 * gather_tiles(g) + 255) / 256, e = (2 * gather_tiles<64>(g) + 255) / 256;
-  return e >= 4 || (p >= 2 * e && (e >= 2 || sizeof(T) == 8));
+  const int waves = p * (g.Vh / g.L[3] > 64 ? 2 : 1);  // of a CU, where k_smear_stout has 4 e
+  return e >= 4 || (waves >= 4 * e && (e >= 2 || sizeof(T) == 8));
 }
 
 template <typename T>
