@@ -210,7 +210,7 @@ def path_stout_form():
     """The kernel of a stout step, by the rounds of 256 blocks that either would take."""
     launches = E.lib().emu_launches
     for L, blocks in (((4, 4, 4, 4), (False, False)), ((2, 2, 2, 66), (False, False)), ((2, 2, 2, 128), (False, True)),
-                      ((2, 2, 2, 258), (True, True))):
+                      ((2, 2, 2, 400), (True, True))):
         for prec in (0, 1):
             U = rounded(field(L, 2260, 1), prec)
             before = launches(b"k_smear_stout")
