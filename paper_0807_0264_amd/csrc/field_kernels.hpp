@@ -9,12 +9,14 @@ namespace mcg {
 // of H half indices through LDS, so that both sides of the copy move in runs: whole sites on the
 // interchange side, H consecutive complex numbers per (mu, parity, k) plane on the other.  Written
 // per link from registers, each lane walked 72 bytes (FP32) of the interchange side by itself and a
-// wave wrote runs of 64 bytes.  24^3x48, FP32 links: pack 88 -> 72 us, unpack 125 -> 85 us; a
-// transform 50 -> 38 us either way (191 MB of links and 96 MB of transform each read and written).
+// wave wrote runs of 64 bytes.  24^3x48, FP32 links: pack 87 -> 81 us, unpack 120 -> 68 us; a
+// transform 53 -> 37 us either way (191 MB of links and 96 MB of transform each read and written).  32
+// half indices: with 64 FP32 links take 82 and 77 us, and a small field waits for the few blocks' longer
+// rounds, 8^3x16 pack 3.8 us with 32, 4.7 with 64, unpack 3.7 and 6.1 (3.6 and 4.3 from registers).
 // LDS holds the matrices of a site at a stride that spreads the sites over the banks.
 // A thread has up to nine loads in flight on either side.
 template <typename T, int NM> struct PackTile {
-  static constexpr int H = sizeof(T) == 4 ? 64 : 32, N = 9 * NM, STRIDE = N | 1;
+  static constexpr int H = 32, N = 9 * NM, STRIDE = N | 1;
   static constexpr int AOS = (2 * H * N + 255) / 256, SOA = (2 * N * H + 255) / 256;  // rounds of 256 on each side
 };
 // the parity of a pair's first site (even x)
