@@ -1924,22 +1924,26 @@ template <typename T> LoopScratch general_scratch(const Geom &g, int tmax) {
   return r;
 }
 
-// The images of each direction's path, formed when first asked for (microseconds of host time each, behind
-// the kernels already launched)
+// The images of each direction's path, formed when asked for (microseconds of host time each, behind the
+// kernels already launched).  The first few are kept, since the choice between the paths asks for them
+// too; a reference holds until the next direction is asked for.
 class Paths {
+  static constexpr int KEPT = 16;
   const int32_t *vec_;
-  std::vector<PathImages> done_;
+  PathImages images_[KEPT + 1];
+  int last_ = -1;  // the direction in images_[KEPT]
 
  public:
   const int n;
   Paths(int nvec, const int32_t *vec) : vec_(vec), n(nvec) {}
   const PathImages &operator[](int i) {
-    while ((int)done_.size() <= i) {
-      const int32_t *v = vec_ + 3 * done_.size();
-      const int w[3] = {v[0], v[1], v[2]};
-      done_.push_back(path_images(staircase_steps(w)));
+    PathImages &p = images_[std::min(i, KEPT)];
+    if (i < KEPT ? p.empty() : last_ != i) {
+      const int v[3] = {vec_[3 * i], vec_[3 * i + 1], vec_[3 * i + 2]};
+      p = path_images(staircase_steps(v));
+      if (i >= KEPT) last_ = i;
     }
-    return done_[i];
+    return p;
   }
 };
 
@@ -2003,8 +2007,9 @@ mcg_status wilson_general(mcg_ctx *ctx, const mcg_field *U, Paths &paths, int rm
 // The loops in the temporal gauge (loops_kernels.hpp): *done is false, and nothing is written to W, when
 // the extents or the scratch do not allow it or a time link is not unitary; the general path then takes
 // the call.  The host reads whether they are as soon as the transform is formed, before it launches the
-// loops: a synchronisation of 10 us, where a call that is refused cost three launches per chunk of
-// images and two copies.
+// loops: a synchronisation, where a call that is refused cost three launches per chunk of images and two
+// copies.  (Waiting for an event instead, with the links' kernel already queued, took 10-17 us more on small
+// lattices and the same on large ones.)
 // Both paths keep their lines and partial sums in one buffer, and as many images share a launch as
 // keep it within what the general path holds, so a call leaves no more scratch behind than that path
 // and leaves it room.  Lattices so large that one image exceeds this (the gauged links are three
@@ -2055,8 +2060,8 @@ mcg_status wilson_gauged(mcg_ctx *ctx, const mcg_field *U, Paths &paths, int rma
   HIPCHK(hipStreamSynchronize(s));
   if (*bad) return MCG_OK;
   double *res = (double *)ctx->wl_res.p;
-  HIPCHK(launch_zero(res, nres, s));
   HIPCHK(launch_wl_links<T>(g, U->ptr, lines, links, plan.TE, s));
+  HIPCHK(launch_zero(res, nres, s));
   for (int i = 0; i < nvec; i++) {
     const PathImages &imgs = paths[i];
     int nimg = 0;
@@ -2096,9 +2101,11 @@ template <typename T>
 bool few_loops(const Geom &g, Paths &paths, int rmax, int tmax) {
   const double product = sizeof(T) == 4 ? 1.8e-5 : 2.8e-5;  // one site's loop, per extent T
   const double gauged = 30.0 + 0.45 * (g.L[3] + tmax) + 2.5e-4 * g.V + 20.0 * (paths.n - 1);
-  double general = 0.0;
-  for (int i = 0; i < paths.n && general < gauged; i++)
-    general += rmax * (11.0 + 2.2 * tmax + product * g.V * paths[i].size() * (tmax + 2));
+  auto direction = [&](size_t images) { return rmax * (11.0 + 2.2 * tmax + product * g.V * images * (tmax + 2)); };
+  double general = paths.n * direction(3);  // at least: no path has fewer images
+  if (general >= gauged) return false;
+  general = 0.0;
+  for (int i = 0; i < paths.n && general < gauged; i++) general += direction(paths[i].size());
   return general < gauged;
 }
 

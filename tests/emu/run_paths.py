@@ -90,6 +90,17 @@ def path_loops_few():
             assert E.lib().emu_launches(b"k_wl_gauge") - before == gauged, (prec, rmax, tmax)
 
 
+def path_loops_directions():
+    """More directions in one call than the library keeps path images of, on either path."""
+    L = (4, 4, 4, 4)
+    vecs = [(1, 0, 0), (1, 1, 0), (1, 1, 1)] * 7
+    for bad in (None, 1.001):
+        U = loop_field(L, 2300, 0, bad)
+        got = E.wilson_loops(E.links(U, 0), vecs, 1, 2)
+        want = O.wilson_loops(U, vecs[:3], 1, 2)
+        assert np.abs(got - np.tile(want, (7, 1, 1))).max() < 1e-13
+
+
 def cold_field(L, prec, steps):
     """Unit links, the time links scaled by 1 + steps * (unit in the last place of 1): W(R, T) is the
     scale to the power 2 T, whatever the path multiplies out."""

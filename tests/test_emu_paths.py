@@ -8,7 +8,7 @@ import pytest
 
 from test_emu import EMU, emu_lib  # noqa: F401
 
-PATHS = ["theta", "loops", "loops_extents", "loops_scaled", "loops_precision", "loops_few", "loops_scratch", "loops_refused", "launch_form", "stout_form", "field_accesses", "backward_workspace"]
+PATHS = ["theta", "loops", "loops_extents", "loops_scaled", "loops_precision", "loops_few", "loops_directions", "loops_scratch", "loops_refused", "launch_form", "stout_form", "field_accesses", "backward_workspace"]
 
 
 @pytest.mark.parametrize("path", PATHS)
